@@ -123,8 +123,12 @@ struct SampleArgs {
   const float* uniforms;   // [B * kp1][2]: acceptance test, draw
   float temperature;
   int top_k;
+  // nullable: [B * kp1][V / 128], the largest logit of each 128-id block (the
+  // LM head's argmax partials)
+  const float* block_max;
   int32_t* row_out;        // [B * kp1][3]: accepted?, token if rejected here, token if last
 };
+void launch_block_max(const float* logits, int rows, int V, float* block_max, hipStream_t st);
 void launch_sample(const SampleArgs& s, int32_t* accept_lens, int32_t* next_tokens, hipStream_t st);
 
 // attention (attn.hip)

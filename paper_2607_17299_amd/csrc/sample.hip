@@ -10,13 +10,26 @@
 // temperature 1 and top-k 200 and requires lossless speculation; the rule is
 // the standard one for a point-mass drafter.)
 //
-// k_sample_rows: one workgroup per row.  A 3-pass radix select on an
-// order-preserving integer image of the logits finds the top_k-th largest
-// value and how many of its ties are kept; ordered passes (each wave walks its
-// own id segment in coalesced 64-id chunks, with wave scans) rank the ties
-// and place both draws.  Each row's outcome (accepted?,
-// token if rejected here, token if every draft up to here is accepted) is
-// computed for every row; k_sample_accept then walks the rows of a request.
+// k_sample_rows: one workgroup per row.  Each row's outcome (accepted?, token
+// if rejected here, token if every draft up to here is accepted) is computed
+// for every row; k_sample_accept then walks the rows of a request.
+//
+// The LM head leaves the largest logit of every 128-id block.  The top_k-th
+// largest of these block maxima is at most the top_k-th largest logit, so every
+// kept id lies in a block whose maximum reaches it and is itself at least that
+// large: sample_from_blocks reads only those blocks (about top_k of the V / 128)
+// and does the rest, an exact 3-pass radix select on an order-preserving integer
+// image of the logits and ordered scans for tie ranks and draws, on the few
+// candidates in LDS.  At top_k 200 of 151,936 ids a row has about 220
+// candidates.  What bounds it is latency: a dozen block-wide scans.  80 rows of
+// 151,936 ids: 454 us with sample_from_row (six passes over all logits),
+// 28.5 us from the block maxima.
+//
+// sample_from_row walks the whole row instead: the radix select over all ids,
+// then ordered passes (each wave walks its own id segment in coalesced 64-id
+// chunks, with wave scans).  It takes what the blocks cannot narrow down: more
+// kept ids than blocks, rows with more candidates than fit LDS (many equal
+// logits), NaN block maxima.
 #include "kernels.h"
 
 namespace {
@@ -24,8 +37,12 @@ namespace {
 constexpr int kST = 1024;   // threads per row workgroup
 constexpr int kBins = 2048; // radix-select bins (11-bit digits)
 
+constexpr int kBlk = 128;       // ids per block maximum (the LM head's column block)
+constexpr int kMaxBlk = 4096;   // block maxima a workgroup handles (4 per thread)
+constexpr int kMaxCand = 4096;  // candidates held in LDS (4 per thread)
+
 __device__ __forceinline__ uint32_t fkey(float x) {
-  const uint32_t u = __float_as_uint(x);
+  const uint32_t u = __float_as_uint(x + 0.f);  // -0 and +0 are the same value
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);  // larger float -> larger key
 }
 
@@ -62,20 +79,267 @@ __device__ __forceinline__ T wave_incl_scan(T x) {
   return x;
 }
 
-__global__ void __launch_bounds__(kST) k_sample_rows(SampleArgs s) {
+// Scan over the block's threads (in thread order) of one float each: thread
+// t's (lower, upper) running sums.  Upper of a thread is bit for bit the lower
+// of the next one, so the intervals tile [0, total) without gaps or overlaps.
+__device__ float2 block_scan_f(float v, float* sh, float* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const float x = wave_incl_scan(v);
+  const float below = __shfl_up(x, 1, 64);
+  __syncthreads();
+  if (lane == 63) sh[w] = x;
+  __syncthreads();
+  float off = 0.f, tot = 0.f;
+  for (int i = 0; i < nw; ++i) {
+    if (i == w) off = tot;
+    tot += sh[i];
+  }
+  *total = tot;
+  __syncthreads();
+  return make_float2(lane ? off + below : off, off + x);
+}
+
+struct SampleShared {
+  int hist[2 * kBins];
+  int sh_i[kST / 64];
+  float sh_f[kST / 64], sh_g[kST / 64];
+  uint32_t prefix;
+  int need;
+  float max, wd;
+  int tok[2];
+  int flag;
+};
+
+// One pass of the radix select after its histogram (nb bins of `bits` at
+// `shift`, two copies in hist): moves to the bin holding the need-th largest.
+// Thread t looks at bins 2t and 2t + 1.
+__device__ void radix_pick(SampleShared& sh, uint32_t pre, int shift, int nb) {
+  const int t = threadIdx.x;
+  const int* hist = sh.hist;
+  const int c1 = 2 * t + 1 < nb ? hist[2 * t + 1] + hist[kBins + 2 * t + 1] : 0;
+  const int c0 = 2 * t < nb ? hist[2 * t] + hist[kBins + 2 * t] : 0;
+  int total;
+  const int below = block_excl_scan_i(c0 + c1, sh.sh_i, &total);
+  const int above = total - below - c0 - c1;  // elements in bins above 2t+1
+  const int need = sh.need;
+  __syncthreads();
+  if (above < need && need <= above + c1) {
+    sh.prefix = pre | ((uint32_t)(2 * t + 1) << shift);
+    sh.need = need - above;
+  } else if (above + c1 < need && need <= above + c1 + c0) {
+    sh.prefix = pre | ((uint32_t)(2 * t) << shift);
+    sh.need = need - above - c1;
+  }
+  __syncthreads();
+}
+
+// The row's outcome from the LM head's block maxima; false (by every thread)
+// when they leave too many candidates or hold a NaN, and nothing is written.
+__device__ bool sample_from_blocks(const SampleArgs& s, int r, int d, SampleShared& sh, uint32_t* c_key, int* c_id) {
   constexpr int NW = kST / 64;
-  __shared__ int hist[2 * kBins];
-  __shared__ int sh_i[NW];
-  __shared__ float sh_f[NW], sh_g[NW];
-  __shared__ uint32_t s_prefix;
-  __shared__ int s_need;
-  __shared__ float s_max, s_wd;
-  __shared__ int s_tok[2], s_last[2];
-  const int r = blockIdx.x;
-  const int b = r / s.kp1, i = r % s.kp1;
-  const int dl = s.ntok[b] - 1;  // drafts of the request (-1: inactive step)
-  if (i > dl) return;
-  const int d = i < dl ? s.drafts[(int64_t)b * s.k_max + i] : -1;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const float* z = s.logits + (int64_t)r * s.V;
+  const int nblk = s.V / kBlk;
+  const float* bm = s.block_max + (int64_t)r * nblk;
+  // the first two digits (22 bits) of the top_k-th largest block maximum: the
+  // low edge of its bin bounds the kept logits from below
+  uint32_t mk[4];
+  bool has[4], nan = false;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int q = 4 * t + e;
+    has[e] = q < nblk;
+    const float v = has[e] ? bm[q] : 0.f;
+    nan |= v != v;
+    mk[e] = fkey(v);
+  }
+  if (t == 0) {
+    sh.prefix = 0;
+    sh.need = s.top_k;
+    sh.flag = 0;
+    sh.tok[0] = sh.tok[1] = 0x7fffffff;
+  }
+  __syncthreads();
+  if (nan) sh.flag = 1;  // every writer stores 1
+  for (int pass = 0; pass < 2; ++pass) {
+    const int shift = pass == 0 ? 21 : 10;
+    for (int k = t; k < 2 * kBins; k += kST) sh.hist[k] = 0;
+    __syncthreads();
+    const uint32_t pre = sh.prefix, hmask = pass == 0 ? 0u : 0xffe00000u;
+    int* hh = sh.hist + (w & 1) * kBins;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (has[e] && (mk[e] & hmask) == pre) atomicAdd(&hh[(mk[e] >> shift) & (kBins - 1)], 1);
+    __syncthreads();
+    radix_pick(sh, pre, shift, kBins);
+  }
+  if (sh.flag) return false;
+  const uint32_t low = sh.prefix;
+  // the blocks that reach it, in id order (c_id holds their list)
+  int nsel;
+  int mine = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) mine += has[e] && mk[e] >= low;
+  int at = block_excl_scan_i(mine, sh.sh_i, &nsel);
+  int* sel = sh.hist;                                  // [nsel] <= kMaxBlk = 2 kBins
+  static_assert(kMaxBlk <= 2 * kBins, "the block list shares the histogram");
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (has[e] && mk[e] >= low) sel[at++] = 4 * t + e;
+  __syncthreads();
+  // candidates per wave (wave w takes selected blocks [w0, w1)): count, then
+  // write at the wave's place, in id order (lane l holds ids l and l + 64)
+  const int per = (nsel + NW - 1) / NW;
+  const int w0 = min(nsel, w * per), w1 = min(nsel, w0 + per);
+  int cnt = 0;
+  for (int q = w0; q < w1; ++q) {
+    const float* zb = z + (int64_t)sel[q] * kBlk + lane;
+    cnt += __popcll(__ballot(fkey(zb[0]) >= low)) + __popcll(__ballot(fkey(zb[64]) >= low));
+  }
+  if (lane == 0) sh.sh_i[w] = cnt;
+  __syncthreads();
+  int pos = 0, nc = 0;
+  for (int k = 0; k < NW; ++k) {
+    if (k < w) pos += sh.sh_i[k];
+    nc += sh.sh_i[k];
+  }
+  __syncthreads();
+  if (nc > kMaxCand) return false;
+  for (int q = w0; q < w1; ++q) {
+    const int id0 = sel[q] * kBlk + lane;
+    const uint32_t k0 = fkey(z[id0]), k1 = fkey(z[id0 + 64]);
+    const unsigned long long b0 = __ballot(k0 >= low), b1 = __ballot(k1 >= low);
+    const unsigned long long before = (1ull << lane) - 1;
+    if (k0 >= low) {
+      const int o = pos + __popcll(b0 & before);
+      c_key[o] = k0;
+      c_id[o] = id0;
+    }
+    pos += __popcll(b0);
+    if (k1 >= low) {
+      const int o = pos + __popcll(b1 & before);
+      c_key[o] = k1;
+      c_id[o] = id0 + 64;
+    }
+    pos += __popcll(b1);
+  }
+  if (t == 0) {
+    sh.prefix = 0;
+    sh.need = s.top_k;
+  }
+  __syncthreads();
+  // thread t owns candidates 4t .. 4t+3 (id order)
+  uint32_t key[4];
+  bool in[4];
+  uint32_t top = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    in[e] = 4 * t + e < nc;
+    key[e] = in[e] ? c_key[4 * t + e] : 0;
+    top = max(top, key[e]);
+  }
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+    const int nb = pass == 2 ? kBins / 2 : kBins;
+    for (int k = t; k < 2 * kBins; k += kST) sh.hist[k] = 0;
+    __syncthreads();
+    const uint32_t pre = sh.prefix;
+    const uint32_t hmask = pass == 0 ? 0u : pass == 1 ? 0xffe00000u : 0xfffffc00u;
+    int* hh = sh.hist + (w & 1) * kBins;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (in[e] && (key[e] & hmask) == pre) atomicAdd(&hh[(key[e] >> shift) & (nb - 1)], 1);
+    __syncthreads();
+    radix_pick(sh, pre, shift, nb);
+  }
+  const uint32_t kth = sh.prefix;   // key of the top_k-th largest logit
+  const int ties_kept = sh.need;    // how many logits equal to it are kept (lowest ids first)
+  for (int o = 32; o >= 1; o >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, o, 64));
+  __syncthreads();
+  if (lane == 0) sh.sh_i[w] = (int)top;
+  __syncthreads();
+  for (int k = 0; k < NW; ++k) top = max(top, (uint32_t)sh.sh_i[k]);
+  auto value = [](uint32_t k) { return __uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k); };
+  const float zmax = value(top), invT = 1.f / s.temperature;
+  int ntie = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) ntie += in[e] && key[e] == kth;
+  int all_ties;
+  int rank = block_excl_scan_i(ntie, sh.sh_i, &all_ties);
+  float wv[4], wr[4], sum = 0.f, sumr = 0.f;
+  int id[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    id[e] = in[e] ? c_id[4 * t + e] : -1;
+    const bool tie = in[e] && key[e] == kth;
+    rank += tie ? 1 : 0;
+    const bool kept = in[e] && (key[e] > kth || (tie && rank <= ties_kept));
+    wv[e] = kept ? expf((value(key[e]) - zmax) * invT) : 0.f;
+    wr[e] = id[e] == d ? 0.f : wv[e];
+    sum += wv[e];
+    sumr += wr[e];
+    if (id[e] == d && in[e]) sh.wd = wv[e];
+  }
+  if (t == 0) sh.flag = 0;
+  float W, Wr;
+  const float2 ce = block_scan_f(sum, sh.sh_f, &W);
+  const float2 cr = block_scan_f(sumr, sh.sh_g, &Wr);
+  // the draft's weight: 0 unless it is a candidate
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (in[e] && id[e] == d) sh.flag = 1;
+  __syncthreads();
+  const float wdraft = sh.flag ? sh.wd : 0.f;
+  const float u = s.uniforms[(int64_t)r * 2], vv = s.uniforms[(int64_t)r * 2 + 1];
+  const float tgt_end = vv * W, tgt_rej = vv * Wr;
+  // the thread whose interval holds a target looks for it among its candidates
+  // (the last kept one takes what rounding leaves at the interval's end)
+  int last_end = -1, last_rej = -1;  // highest kept ids (fallback below)
+  int hit_end = -1, hit_rej = -1;
+  float pe = ce.x, pr = cr.x;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    pe += wv[e];
+    pr += wr[e];
+    if (wv[e] > 0.f) {
+      last_end = id[e];
+      if (hit_end < 0 && pe > tgt_end) hit_end = id[e];
+    }
+    if (wr[e] > 0.f) {
+      last_rej = id[e];
+      if (hit_rej < 0 && pr > tgt_rej) hit_rej = id[e];
+    }
+  }
+  if (ce.x <= tgt_end && tgt_end < ce.y && last_end >= 0) atomicMin(&sh.tok[1], hit_end >= 0 ? hit_end : last_end);
+  if (cr.x <= tgt_rej && tgt_rej < cr.y && last_rej >= 0) atomicMin(&sh.tok[0], hit_rej >= 0 ? hit_rej : last_rej);
+  // a target that rounds to the total lies in no interval: the last kept token
+  for (int o = 32; o >= 1; o >>= 1) {
+    last_end = max(last_end, __shfl_xor(last_end, o, 64));
+    last_rej = max(last_rej, __shfl_xor(last_rej, o, 64));
+  }
+  if (lane == 0) {
+    sh.sh_i[w] = last_end;
+    sh.hist[w] = last_rej;
+  }
+  __syncthreads();
+  if (t == 0) {
+    int le = -1, lr = -1;
+    for (int k = 0; k < NW; ++k) {
+      le = max(le, sh.sh_i[k]);
+      lr = max(lr, sh.hist[k]);
+    }
+    int* o = s.row_out + (int64_t)r * 3;
+    o[0] = d >= 0 && u * W < wdraft ? 1 : 0;
+    o[1] = sh.tok[0] != 0x7fffffff ? sh.tok[0] : lr;
+    o[2] = sh.tok[1] != 0x7fffffff ? sh.tok[1] : le;
+  }
+  return true;
+}
+
+__device__ void sample_from_row(const SampleArgs& s, int r, int d, SampleShared& sh) {
+  constexpr int NW = kST / 64;
+  int *hist = sh.hist, *sh_i = sh.sh_i, *s_tok = sh.tok;
+  float *sh_f = sh.sh_f, *sh_g = sh.sh_g;
   const float* z = s.logits + (int64_t)r * s.V;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
 
@@ -84,9 +348,8 @@ __global__ void __launch_bounds__(kST) k_sample_rows(SampleArgs s) {
   // bits, so that logits of similar size spread over many bins), into two
   // histogram copies (even and odd waves) to halve atomic contention
   if (t == 0) {
-    s_prefix = 0;
-    s_need = s.top_k;
-    s_wd = 0.f;
+    sh.prefix = 0;
+    sh.need = s.top_k;
     s_tok[0] = s_tok[1] = -1;
   }
   float mx = -INFINITY;
@@ -96,7 +359,7 @@ __global__ void __launch_bounds__(kST) k_sample_rows(SampleArgs s) {
     const int nb = 1 << nbits;
     for (int k = t; k < 2 * kBins; k += kST) hist[k] = 0;
     __syncthreads();
-    const uint32_t pre = s_prefix;
+    const uint32_t pre = sh.prefix;
     const uint32_t hmask = pass == 0 ? 0u : (0xffffffffu << (shift + nbits));
     int* hh = hist + (w & 1) * kBins;
     for (int v = t; v < s.V; v += kST) {
@@ -106,25 +369,10 @@ __global__ void __launch_bounds__(kST) k_sample_rows(SampleArgs s) {
       if ((key & hmask) == pre) atomicAdd(&hh[(key >> shift) & (nb - 1)], 1);
     }
     __syncthreads();
-    // the bin holding the need-th largest: thread t looks at bins 2t and 2t+1
-    const int c1 = 2 * t + 1 < nb ? hist[2 * t + 1] + hist[kBins + 2 * t + 1] : 0;
-    const int c0 = 2 * t < nb ? hist[2 * t] + hist[kBins + 2 * t] : 0;
-    int total;
-    const int below = block_excl_scan_i(c0 + c1, sh_i, &total);
-    const int above = total - below - c0 - c1;  // elements in bins above 2t+1
-    const int need = s_need;
-    __syncthreads();
-    if (above < need && need <= above + c1) {
-      s_prefix = pre | ((uint32_t)(2 * t + 1) << shift);
-      s_need = need - above;
-    } else if (above + c1 < need && need <= above + c1 + c0) {
-      s_prefix = pre | ((uint32_t)(2 * t) << shift);
-      s_need = need - above - c1;
-    }
-    __syncthreads();
+    radix_pick(sh, pre, shift, nb);
   }
-  const uint32_t kth = s_prefix;  // key of the top_k-th largest logit
-  const int ties_kept = s_need;   // how many logits equal to it are kept (lowest ids first)
+  const uint32_t kth = sh.prefix;  // key of the top_k-th largest logit
+  const int ties_kept = sh.need;   // how many logits equal to it are kept (lowest ids first)
   // row maximum
   for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
   if (lane == 0) sh_f[w] = mx;
@@ -132,10 +380,10 @@ __global__ void __launch_bounds__(kST) k_sample_rows(SampleArgs s) {
   if (t == 0) {
     float m = sh_f[0];
     for (int k = 1; k < NW; ++k) m = fmaxf(m, sh_f[k]);
-    s_max = m;
+    sh.max = m;
   }
   __syncthreads();
-  const float zmax = s_max;
+  const float zmax = sh.max;
   const float invT = 1.f / s.temperature;
 
   // ---- ordered passes: wave w owns ids [seg0, seg1), walked in 64-id chunks
@@ -249,6 +497,32 @@ __global__ void __launch_bounds__(kST) k_sample_rows(SampleArgs s) {
   }
 }
 
+// BLOCKS: the LM head's block maxima are there and can narrow the row down.
+template <bool BLOCKS>
+__global__ void __launch_bounds__(kST) k_sample_rows(SampleArgs s) {
+  __shared__ SampleShared sh;
+  __shared__ uint32_t c_key[BLOCKS ? kMaxCand : 1];
+  __shared__ int c_id[BLOCKS ? kMaxCand : 1];
+  const int r = blockIdx.x;
+  const int b = r / s.kp1, i = r % s.kp1;
+  const int dl = s.ntok[b] - 1;  // drafts of the request (-1: inactive step)
+  if (i > dl) return;
+  const int d = i < dl ? s.drafts[(int64_t)b * s.k_max + i] : -1;
+  if constexpr (BLOCKS) {
+    if (sample_from_blocks(s, r, d, sh, c_key, c_id)) return;
+    __syncthreads();
+  }
+  sample_from_row(s, r, d, sh);
+}
+
+// block_max[row][block] over rows of V logits (V a multiple of kBlk): what the
+// LM head's epilogue leaves, for logits that come from elsewhere.
+__global__ void __launch_bounds__(64) k_block_max(const float* z, int V, float* block_max) {
+  const int64_t at = (int64_t)blockIdx.y * V + (int64_t)blockIdx.x * kBlk + threadIdx.x;
+  const float m = wave_max(fmaxf(z[at], z[at + 64]));
+  if (threadIdx.x == 0) block_max[(int64_t)blockIdx.y * (V / kBlk) + blockIdx.x] = m;
+}
+
 __global__ void k_sample_accept(SampleArgs s, int32_t* accept_lens, int32_t* next_tokens) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= s.B) return;
@@ -273,6 +547,17 @@ __global__ void k_sample_accept(SampleArgs s, int32_t* accept_lens, int32_t* nex
 }  // namespace
 
 void launch_sample(const SampleArgs& s, int32_t* accept_lens, int32_t* next_tokens, hipStream_t st) {
-  k_sample_rows<<<s.B * s.kp1, kST, 0, st>>>(s);
+  // A block maximum bounds the kept logits only when there are at least top_k
+  // of them; a workgroup handles kMaxBlk.  (A vocabulary of 4096 ids has 32
+  // blocks: sample_from_row reads its 16 KB row from LDS-speed caches anyway.)
+  const int nblk = s.block_max && s.V % kBlk == 0 ? s.V / kBlk : 0;
+  if (s.top_k <= nblk && nblk <= kMaxBlk)
+    k_sample_rows<true><<<s.B * s.kp1, kST, 0, st>>>(s);
+  else
+    k_sample_rows<false><<<s.B * s.kp1, kST, 0, st>>>(s);
   k_sample_accept<<<cdiv_i(s.B, 64), 64, 0, st>>>(s, accept_lens, next_tokens);
+}
+
+void launch_block_max(const float* logits, int rows, int V, float* block_max, hipStream_t st) {
+  k_block_max<<<dim3(V / kBlk, rows), 64, 0, st>>>(logits, V, block_max);
 }

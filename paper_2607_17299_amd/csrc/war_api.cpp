@@ -1028,6 +1028,7 @@ war_status verify_impl(war_model* m, war_kv_pool* p, int32_t B, const int32_t* s
     sa.uniforms = sp.uniforms;
     sa.temperature = sp.temperature;
     sa.top_k = sp.top_k;
+    sa.block_max = w.amax_v;
     sa.row_out = m->row_out.as<int32_t>();
     Timed t(m->prof, st, "sample_accept");
     launch_sample(sa, accept_lens, next_tokens, st);
@@ -1354,9 +1355,19 @@ war_status war_debug_sample(const float* logits, int32_t V, int32_t B, int32_t k
   sa.temperature = temperature;
   sa.top_k = top_k;
   sa.row_out = rows.as<int32_t>();
+  DevBuf bmax;  // the block maxima that a step has from its LM head
+  if (V % 128 == 0) {
+    if (hipError_t e0 = bmax.ensure((size_t)B * (k_max + 1) * (V / 128) * 4); e0 != hipSuccess) {
+      rows.release();
+      return fail(WAR_ERR_HIP, std::string("block maxima: ") + hipGetErrorString(e0));
+    }
+    launch_block_max(logits, B * (k_max + 1), V, bmax.as<float>(), st);
+    sa.block_max = bmax.as<float>();
+  }
   launch_sample(sa, accept_lens, next_tokens, st);
   const hipError_t e = hipStreamSynchronize(st);
   rows.release();
+  bmax.release();
   HIPCHK(e);
   return WAR_OK;
 }

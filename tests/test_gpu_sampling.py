@@ -12,10 +12,12 @@ from oracle.sampling import filtered_probs, verify_sampled
 pytestmark = pytest.mark.gpu
 
 
-def _case(V, B, k, T, top_k, scale, seed, ties=False):
+def _case(V, B, k, T, top_k, scale, seed, ties=False, alter=None):
     from paper_2607_17299_amd import war
     rng = np.random.default_rng(seed)
     z = (rng.standard_normal((B * (k + 1), V)) * scale).astype(np.float32)
+    if alter:
+        alter(z, rng)
     if ties:
         # exact ties at the top_k boundary and at the maximum
         for r in range(z.shape[0]):
@@ -68,3 +70,37 @@ def test_sampling_kernels_ties_at_the_boundary():
     """Exact ties at the top_k boundary (kept by lowest id) and at the maximum."""
     exact, report, _ = _case(4096, 24, 4, 1.0, 200, 2.0, seed=99, ties=True)
     assert exact + len(report) == 24 and len(report) <= 1, report
+
+
+def _signed_zeros(z, rng):
+    """Everything kept is +0 or -0 (one value): ties by id across block maxima."""
+    z[:] = np.where(rng.random(z.shape) < 0.01, np.where(rng.random(z.shape) < 0.5, 0.0, -0.0), -1.0 - np.abs(z))
+
+
+def _one_block(z, rng):
+    """Every large logit in one 128-id block: the other blocks' maxima set the bound."""
+    z[:, 256:384] += 30.0
+
+
+def _equal(z, rng):
+    z[:] = 1.5        # more candidates than a workgroup holds: the row path
+
+
+def _infinite(z, rng):
+    z[rng.random(z.shape) < 0.9] = -np.inf
+
+
+@pytest.mark.parametrize("V,top_k,alter", [
+    (151936, 1187, None),          # as many kept ids as 128-id blocks
+    (151936, 1188, None),          # one more: the row path
+    (128, 1, None), (384, 3, None),
+    (4096 * 128, 200, None),       # the most blocks a workgroup handles
+    (4097 * 128, 200, None),       # one more: the row path
+    (4096 + 64, 20, None),         # not whole blocks: the row path
+    (32768, 200, _signed_zeros), (32768, 100, _one_block), (32768, 200, _equal), (32768, 256, _infinite),
+])
+def test_sampling_block_bound_edges(V, top_k, alter):
+    """The block-maximum path and its limits give the rule's decisions (margins
+    below 1e-5, fp32 sums against float64, are reported)."""
+    exact, report, _ = _case(V, 4, 2, 1.0, top_k, 2.0, seed=V + top_k, alter=alter)
+    assert exact + len(report) == 4 and len(report) <= 1, report
