@@ -1,9 +1,11 @@
 // Skinny-M bf16 GEMM on gfx950 MFMA for the decoder projections and the LM head.
 //
 // C[m][n] = sum_k A[m][k] * W[n][k]: A is the (few-row) activation matrix,
-// W a weight matrix stored [out][in].  In the verify step M is 4..~600 rows
+// W a weight matrix stored [out][in].  In most verify steps M is 1..80 rows
 // against N x K weights of 16-310 MB, so the kernel is bound by streaming W
-// from HBM: every weight byte is read exactly once per m-block.
+// from HBM: every weight byte is read exactly once.  (More rows run in
+// gemm_tile.hip: at 96 rows qkv 14.9 -> 12.5 us, o 11.3 -> 10.2, down 25.2 ->
+// 22.8, gate/up 40.7 -> 41; at 80 rows gate/up and qkv are slower there.)
 //
 // Weights are repacked once, when the model is created, into MFMA fragment
 // order: for n-tile nt (16 output rows), k-step s (64 inputs) and half j, the
@@ -39,10 +41,9 @@
 // best (value, lowest index) of each row within each 128-column block.  The
 // SwiGLU epilogue (gate/up, one split) takes the paired [gate; up] groups,
 // wave w of block nb owning gate n-tile 4nb + w and the matching up n-tile,
-// and writes bf16 silu(gate) * up for its 16 columns.  At 97-192 rows the
-// argmax epilogue runs in k_gemm_x2, and SwiGLU and the partial sums of
-// splits of 8-64 k-steps in k_gemm_x2c (below); k_gemm_x2c also takes 33-64
-// rows (SwiGLU and partial sums) and the 8- and 16-step splits at 65-80 rows.
+// and writes bf16 silu(gate) * up for its 16 columns.  At 33-64 rows SwiGLU and
+// the partial sums of splits of 8-64 k-steps run in k_gemm_x2c (below), which
+// also takes the 8- and 16-step splits at 65-80 rows.
 #include "kernels.h"
 
 namespace {
@@ -61,40 +62,17 @@ struct Tile {
 // fully unrolled (straight-line code lets the compiler's memory-counter waits
 // stay exact, so loads issued three steps ahead really stay in flight);
 // NSTEPS == 0: a runtime loop over (K split) / 64 steps.
-// MW = 2: two groups of 4 waves take the two m-blocks of one weight block in
-// one workgroup (rows 97-192: one workgroup per CU instead of 1.5); both read
-// the same W fragments, the second group mostly from L1/L2.
-// WNT: the launch has one m-block, so each weight byte is used by a single
-// workgroup and the weight loads are non-temporal (they do not displace the
-// activations and partial sums that other workgroups reuse; 64-80-row steps
-// 0.14-0.28 ms faster).  With several m-blocks (the append's row chunks) the
-// m-blocks of a weight block find it in L2, so the loads stay temporal.
-template <int MT, int NSTEPS, int EPI, int MW, bool WNT = false>
-__global__ void __launch_bounds__(256 * MW) __attribute__((amdgpu_waves_per_eu(1, 2))) k_gemm(GemmArgs g) {
-  static_assert(MW == 1 || EPI != EPI_ARGMAX, "the argmax epilogue has one m-block per workgroup");
-  __shared__ __attribute__((aligned(16))) unsigned char sAll[MW][3][Tile<MT>::BYTES];
-  const int tid = threadIdx.x & 255, lane = tid & 63, w = tid >> 6, ln = lane & 15, lg = lane >> 4;
-  const int mg = MW > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
-  unsigned char (*sA)[Tile<MT>::BYTES] = sAll[mg];
-  // Workgroups are dealt to the 8 XCDs round-robin by linear id.  The m-blocks
-  // of one weight block get ids 8 apart (same XCD, dispatched together), so
-  // all but the first find W in that XCD's L2; a ragged tail of fewer than 8
-  // n-blocks falls back to consecutive ids.
-  const int mblocks = (g.M + MT * 16 * MW - 1) / (MT * 16 * MW);  // workgroup m-blocks
-  const int NB = g.N / 128;
-  const int full = (NB / 8) * 8 * mblocks;
-  int nb, mb;
-  if ((int)blockIdx.x < full) {
-    const int r = blockIdx.x % (8 * mblocks);
-    nb = (blockIdx.x / (8 * mblocks)) * 8 + (r & 7);
-    mb = r >> 3;
-  } else {
-    const int r = blockIdx.x - full;
-    nb = (NB / 8) * 8 + r / mblocks;
-    mb = r % mblocks;
-  }
+// The launch has one m-block, so each weight byte is used by a single workgroup
+// and the weight loads are non-temporal (they do not displace the activations
+// and partial sums that other workgroups reuse; 64-80-row steps 0.14-0.28 ms
+// faster).
+template <int MT, int NSTEPS, int EPI>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) k_gemm(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) unsigned char sA[3][Tile<MT>::BYTES];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, ln = lane & 15, lg = lane >> 4;
+  const int nb = blockIdx.x;
   const int split = blockIdx.y;
-  const int m0 = (mb * MW + mg) * MT * 16;
+  constexpr int m0 = 0;
   const int kb = split * g.kper;
   const int ke = min(g.K, kb + g.kper);
   const int nsteps = NSTEPS > 0 ? NSTEPS : (ke - kb) / KS;
@@ -136,7 +114,7 @@ __global__ void __launch_bounds__(256 * MW) __attribute__((amdgpu_waves_per_eu(1
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
   };
   auto bload_w = [](__amdgpu_buffer_rsrc_t r, int voff, int soff) {  // cache policy 2: non-temporal
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, WNT ? 2 : 0));
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 2));
   };
   auto load_w = [&](uint4* wr, int s) {
     const int so = (int)((s0 + s) * sstride);
@@ -290,276 +268,15 @@ __global__ void __launch_bounds__(256 * MW) __attribute__((amdgpu_waves_per_eu(1
   }
 }
 
-// The SwiGLU and argmax epilogues at 97-192 rows (two m-blocks of MT = 4..6
-// m-tiles, an m-half each): one 8-wave workgroup takes both m-blocks of its
-// weight block.  Wave (m, h, c) owns m-half m, k-half h of every 64-wide
-// k-step and the 64 columns of half c (four n-tiles: t = 4c .. 4c+3, or gate
-// tiles 2c, 2c+1 with the matching up tiles), so each A fragment it reads
-// from LDS feeds four MFMAs.  The two k-half waves of each (m-half, column
-// half) add their sums through LDS at the end; wave (m, h, c) then writes
-// m-tiles [h ? ceil(MT/2) : 0, h ? MT : ceil(MT/2)) of its m-half.  Same
-// pipeline as k_gemm.  (Measured against k_gemm's two-group mode: gate/up 5%
-// and the LM head 10% faster at 192 rows; the split-K projections slower, so
-// they kept k_gemm.  Gate/up over 64 k-steps and the split-K projections now
-// run in k_gemm_x2c; this kernel keeps the LM head and gate/up over other K.)
-template <int MT, int NSTEPS, int EPI>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) k_gemm_x2(GemmArgs g) {
-  constexpr int RT = 2 * MT;                             // m-tiles of the workgroup
-  constexpr int A_CHUNKS = RT * 16 * (KS / 8);           // 16-byte chunks of the A tile
-  constexpr int A_PER = (A_CHUNKS + 511) / 512;
-  constexpr int A_BYTES = RT * 16 * ROWB;
-  constexpr int MLO = (MT + 1) / 2;                      // m-tiles the k-half 0 waves write
-  constexpr int X_BYTES = 2 * 2 * MT * 4 * 64 * 16;      // the k-half exchange
-  constexpr int S_BYTES = 3 * A_BYTES > X_BYTES ? 3 * A_BYTES : X_BYTES;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[S_BYTES];
-  __shared__ float s_bv[2][RT * 16];                     // argmax: best per column half
-  __shared__ int s_bi[2][RT * 16];
-  auto sA = [&](int buf) { return smem + buf * A_BYTES; };
-  const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, lg = lane >> 4;
-  const int wi = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int mh = wi >> 2, kh = (wi >> 1) & 1, cw = wi & 1;  // m-half, k-half, column half
-  // Workgroups are dealt to the 8 XCDs round-robin by linear id.  The m-blocks
-  // of one weight block get ids 8 apart (same XCD, dispatched together), so
-  // all but the first find W in that XCD's L2; a ragged tail of fewer than 8
-  // n-blocks falls back to consecutive ids.
-  const int mblocks = (g.M + RT * 16 - 1) / (RT * 16);
-  const int NB = g.N / 128;
-  const int full = (NB / 8) * 8 * mblocks;
-  int nb, mb;
-  if ((int)blockIdx.x < full) {
-    const int r = blockIdx.x % (8 * mblocks);
-    nb = (blockIdx.x / (8 * mblocks)) * 8 + (r & 7);
-    mb = r >> 3;
-  } else {
-    const int r = blockIdx.x - full;
-    nb = (NB / 8) * 8 + r / mblocks;
-    mb = r % mblocks;
-  }
-  const int split = blockIdx.y;
-  const int m0 = mb * RT * 16;            // the workgroup's first row
-  const int mr = m0 + mh * MT * 16;       // this wave's m-half
-  const int kb = split * g.kper;
-  const int ke = min(g.K, kb + g.kper);
-  const int nsteps = NSTEPS > 0 ? NSTEPS : (ke - kb) / KS;
-  const int n0 = nb * 128;
-  // SwiGLU: the block's first gate tile (output column tile of the epilogue)
-  const int tb = nb * 4;
-  const bf16_t* Wb = g.Wp + (int64_t)nb * (8 * KS * 16);
-  const int NG = g.N / 128;  // groups; one k-step of all groups is contiguous
-
-  // Loads are raw buffer loads (one descriptor for the W block, one for A): the
-  // compiler does not re-issue them next to their use, so they stay in flight
-  // for the steps in between.  A rows at or beyond M load row 0 instead (no
-  // per-lane branch around the load): an output row depends only on its own A
-  // row, and rows >= M are never written.
-  const __amdgpu_buffer_rsrc_t wres =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Wb), 0, 0x7fffffff, 0x00020000);
-  const __amdgpu_buffer_rsrc_t ares =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(g.A), 0, 0x7fffffff, 0x00020000);
-  // tile t of the group holds half j at byte (t*2 + j)*1024 of a step's piece;
-  // this wave's four tiles (two gate and the two matching up tiles for SwiGLU)
-  int tt[4];
-#pragma unroll
-  for (int n = 0; n < 4; ++n) tt[n] = EPI == EPI_SWIGLU ? (n < 2 ? 2 * cw + n : 4 + 2 * cw + n - 2) : 4 * cw + n;
-  const int64_t sstride = (int64_t)NG * (KS * 256);  // bytes per k-step of the matrix
-  const int s0 = kb / KS;
-  int av[A_PER];
-  int aoff[A_PER];
-#pragma unroll
-  for (int i = 0; i < A_PER; ++i) {
-    const int c = min(tid + 512 * i, A_CHUNKS - 1);
-    const int r = c >> 3, q = c & 7;
-    const int gm = m0 + r;
-    aoff[i] = r * ROWB + q * 16;
-    const int src = gm < g.M ? (g.a_rows ? g.a_rows[gm] : gm) : (g.a_rows ? g.a_rows[0] : 0);
-    av[i] = (src * g.lda + kb + q * 8) * 2;
-  }
-
-  auto bload = [](__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-  };
-  auto load_w = [&](uint4* wr, int s) {
-    const int so = (int)((s0 + s) * sstride);
-#pragma unroll
-    for (int n = 0; n < 4; ++n) wr[n] = bload(wres, (tt[n] * 2 + kh) * 1024 + lane * 16, so);
-  };
-  auto load_a = [&](uint4* ar, int s) {
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i) ar[i] = bload(ares, av[i], s * KS * 2);
-  };
-  auto store_a = [&](const uint4* ar, int buf) {
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i)
-      if (A_CHUNKS % 512 == 0 || tid + 512 * i < A_CHUNKS)
-        *reinterpret_cast<uint4*>(sA(buf) + aoff[i]) = ar[i];
-  };
-
-  f32x4 acc[MT][4];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int n = 0; n < 4; ++n) acc[mt][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  auto compute = [&](const uint4* wr, int buf) {
-    bf16x8 b[4];
-#pragma unroll
-    for (int n = 0; n < 4; ++n) b[n] = as_bf16x8(wr[n]);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const bf16x8 a =
-          as_bf16x8(*reinterpret_cast<const uint4*>(sA(buf) + ((mh * MT + mt) * 16 + ln) * ROWB + lg * 32 + kh * 16));
-#pragma unroll
-      for (int n = 0; n < 4; ++n) acc[mt][n] = mfma16(a, b[n], acc[mt][n]);
-    }
-  };
-
-  // register sets rotate with period 3: step s uses wr[s%3]; ar[s%3] holds A(s)
-  // until it is stored, then receives A(s+3)
-  uint4 wA[4], wB[4], wC[4];
-  uint4 aA[A_PER], aB[A_PER], aC[A_PER];
-  if (nsteps > 0) { load_a(aA, 0); load_w(wA, 0); }
-  if (nsteps > 1) { load_a(aB, 1); load_w(wB, 1); }
-  if (nsteps > 2) { load_a(aC, 2); load_w(wC, 2); }
-  __builtin_amdgcn_sched_barrier(0);
-  if (nsteps > 0) store_a(aA, 0);
-  __syncthreads();
-
-// sched_barrier pins the loads where they are issued: otherwise the scheduler
-// sinks each load next to its use and the step waits for it right away.
-#define GEMM_STEP(S, AL, AS, WR_, B)                   \
-  if ((S) < nsteps) {                                  \
-    if ((S) + 3 < nsteps) load_a(AL, (S) + 3);         \
-    __builtin_amdgcn_sched_barrier(0);                 \
-    compute(WR_, B);                                   \
-    if ((S) + 3 < nsteps) load_w(WR_, (S) + 3);        \
-    __builtin_amdgcn_sched_barrier(0);                 \
-    if ((S) + 1 < nsteps) store_a(AS, ((B) + 1) % 3);  \
-    __syncthreads();                                   \
-  }
-  if constexpr (NSTEPS > 0) {
-#pragma unroll
-    for (int s = 0; s < NSTEPS; s += 3) {
-      GEMM_STEP(s, aA, aB, wA, 0)
-      GEMM_STEP(s + 1, aB, aC, wB, 1)
-      GEMM_STEP(s + 2, aC, aA, wC, 2)
-    }
-  } else {
-    for (int s = 0; s < nsteps; s += 3) {
-      GEMM_STEP(s, aA, aB, wA, 0)
-      GEMM_STEP(s + 1, aB, aC, wB, 1)
-      GEMM_STEP(s + 2, aC, aA, wC, 2)
-    }
-  }
-#undef GEMM_STEP
-
-  // k-half sums: each wave hands the m-tiles the other k-half wave of its
-  // column half writes to LDS, then adds the ones handed to it (the last step's
-  // barrier has ended every read of the A buffers)
-  f32x4* xs = reinterpret_cast<f32x4*>(smem);
-  auto mine = [&](int mt) { return (mt < MLO ? 0 : 1) == kh; };
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-    if (!mine(mt))
-#pragma unroll
-      for (int n = 0; n < 4; ++n) xs[(((mh * 2 + cw) * MT + mt) * 4 + n) * 64 + lane] = acc[mt][n];
-  __syncthreads();
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-    if (mine(mt))
-#pragma unroll
-      for (int n = 0; n < 4; ++n) acc[mt][n] += xs[(((mh * 2 + cw) * MT + mt) * 4 + n) * 64 + lane];
-
-  // lane holds C[mt*16 + lg*4 + i][column of tile tt[n]: n0 + tt[n]*16 + ln]
-  if constexpr (EPI == EPI_SWIGLU) {
-    // n = 0, 1: gate tiles 2cw + n; n = 2, 3: the matching up tiles
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      if (!mine(mt)) continue;
-#pragma unroll
-      for (int n = 0; n < 2; ++n)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int m = mr + mt * 16 + lg * 4 + i;
-          const float a = acc[mt][n][i];
-          if (m < g.M)
-            g.out[(int64_t)m * g.ld_out + (tb + 2 * cw + n) * 16 + ln] = f2bf(a / (1.f + expf(-a)) * acc[mt][n + 2][i]);
-        }
-    }
-  } else if constexpr (EPI == EPI_PARTIAL) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      if (!mine(mt)) continue;
-#pragma unroll
-      for (int n = 0; n < 4; ++n)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int m = mr + mt * 16 + lg * 4 + i;
-          if (m < g.M) g.P[((int64_t)split * g.M + m) * g.N + n0 + tt[n] * 16 + ln] = acc[mt][n][i];
-        }
-    }
-  } else {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      if (!mine(mt)) continue;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = (mh * MT + mt) * 16 + lg * 4 + i;
-        const int m = m0 + r;
-        // columns ascend with n: a strictly larger value replaces, ties keep the lower id
-        float v = acc[mt][0][i];
-        int idx = n0 + tt[0] * 16 + ln;
-#pragma unroll
-        for (int n = 1; n < 4; ++n)
-          if (acc[mt][n][i] > v) {
-            v = acc[mt][n][i];
-            idx = n0 + tt[n] * 16 + ln;
-          }
-        if (g.logits && m < g.M)
-#pragma unroll
-          for (int n = 0; n < 4; ++n) g.logits[(int64_t)m * g.ld_logits + n0 + tt[n] * 16 + ln] = acc[mt][n][i];
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-          const float ov = __shfl_xor(v, o, 64);
-          const int oi = __shfl_xor(idx, o, 64);
-          if (ov > v || (ov == v && oi < idx)) {
-            v = ov;
-            idx = oi;
-          }
-        }
-        if (ln == 0) {
-          s_bv[cw][r] = v;
-          s_bi[cw][r] = idx;
-        }
-      }
-    }
-    __syncthreads();
-    for (int r = tid; r < RT * 16; r += 512) {
-      const int m = m0 + r;
-      if (m >= g.M) continue;
-      float v = s_bv[0][r];
-      int idx = s_bi[0][r];
-      if (s_bv[1][r] > v || (s_bv[1][r] == v && s_bi[1][r] < idx)) {
-        v = s_bv[1][r];
-        idx = s_bi[1][r];
-      }
-      g.amax_v[(int64_t)m * (g.N / 128) + nb] = v;
-      g.amax_i[(int64_t)m * (g.N / 128) + nb] = idx;
-    }
-  }
-}
-
-// SwiGLU (one split of 64 k-steps) and split-K partial sums at 33-192 rows,
+// SwiGLU (one split of 64 k-steps) and split-K partial sums at 33-80 rows,
 // column-quarter waves: wave (kh, cq) owns k-half kh of every step and two
 // n-tiles (gate tile cq with its up tile 4 + cq, or tiles 2cq, 2cq + 1) for
 // all RT m-tiles (one A fragment read from LDS feeds two MFMAs), so no
 // two waves load the same weight fragment and every weight byte is used by one
-// workgroup (WNT: non-temporal weight loads).  The two k-halves' sums meet in
+// workgroup (non-temporal weight loads).  The two k-halves' sums meet in
 // LDS at the end, the kh = 0 waves writing the first ceil(RT/2) m-tiles and
-// the kh = 1 waves the rest.  Gate/up at 100, 128
-// and 192 rows: 45, 50 and 59 us against 56, 56 and 61 us for k_gemm_x2; at
-// 192 rows qkv 21.8 -> 20.7 us, o 16.4 -> 15.2, down 35.8 -> 32.1 against
-// k_gemm's two-group mode (weights rotated past the memory-side cache).
-template <int RT, int NSTEPS, int EPI, bool WNT>
+// the kh = 1 waves the rest.
+template <int RT, int NSTEPS, int EPI>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) k_gemm_x2c(GemmArgs g) {
   static_assert(EPI == EPI_SWIGLU || EPI == EPI_PARTIAL, "SwiGLU or partial sums");
   constexpr int A_CHUNKS = RT * 16 * (KS / 8);
@@ -573,20 +290,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))
   const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, lg = lane >> 4;
   const int wi = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kh = wi >> 2, cq = wi & 3;
-  const int mblocks = (g.M + RT * 16 - 1) / (RT * 16);
-  const int NB = g.N / 128;
-  const int full = (NB / 8) * 8 * mblocks;
-  int nb, mb;
-  if ((int)blockIdx.x < full) {
-    const int r = blockIdx.x % (8 * mblocks);
-    nb = (blockIdx.x / (8 * mblocks)) * 8 + (r & 7);
-    mb = r >> 3;
-  } else {
-    const int r = blockIdx.x - full;
-    nb = (NB / 8) * 8 + r / mblocks;
-    mb = r % mblocks;
-  }
-  const int m0 = mb * RT * 16;
+  const int nb = blockIdx.x;
+  constexpr int m0 = 0;
   const int split = blockIdx.y;
   const int kb = split * g.kper;
   const int s0 = kb / KS;
@@ -617,7 +322,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
   };
   auto bload_w = [](__amdgpu_buffer_rsrc_t r, int voff, int soff) {  // cache policy 2: non-temporal
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, WNT ? 2 : 0));
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 2));
   };
   auto load_w = [&](uint4* wr, int s) {
     const int so = (int)((s0 + s) * sstride);
@@ -712,71 +417,31 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))
   }
 }
 
-template <int MT, int MW, bool WNT>
-void launch_mw(const GemmArgs& g, int epi, int splits, hipStream_t st) {
-  dim3 grid((g.N / 128) * cdiv_i(g.M, MT * 16 * MW), splits, 1);
-  const dim3 block(256 * MW);
-  const int steps = g.kper / KS;
-  const bool exact = (int64_t)g.kper * splits == g.K;
-  if (epi == EPI_SWIGLU) {
-    if (steps == 64) k_gemm<MT, 64, EPI_SWIGLU, MW, WNT><<<grid, block, 0, st>>>(g);
-    else k_gemm<MT, 0, EPI_SWIGLU, MW, WNT><<<grid, block, 0, st>>>(g);
-  } else if (exact && steps == 4) {
-    k_gemm<MT, 4, EPI_PARTIAL, MW, WNT><<<grid, block, 0, st>>>(g);
-  } else if (exact && steps == 8) {
-    k_gemm<MT, 8, EPI_PARTIAL, MW, WNT><<<grid, block, 0, st>>>(g);
-  } else if (exact && steps == 12) {
-    k_gemm<MT, 12, EPI_PARTIAL, MW, WNT><<<grid, block, 0, st>>>(g);
-  } else if (exact && steps == 16) {
-    k_gemm<MT, 16, EPI_PARTIAL, MW, WNT><<<grid, block, 0, st>>>(g);
-  } else if (exact && steps == 32) {
-    k_gemm<MT, 32, EPI_PARTIAL, MW, WNT><<<grid, block, 0, st>>>(g);
-  } else if (exact && steps == 48) {
-    k_gemm<MT, 48, EPI_PARTIAL, MW, WNT><<<grid, block, 0, st>>>(g);
-  } else if (exact && steps == 64) {
-    k_gemm<MT, 64, EPI_PARTIAL, MW, WNT><<<grid, block, 0, st>>>(g);
-  } else {
-    k_gemm<MT, 0, EPI_PARTIAL, MW, WNT><<<grid, block, 0, st>>>(g);
-  }
-}
-
 template <int MT>
 void launch_mt(const GemmArgs& g, int epi, int splits, hipStream_t st) {
-  if constexpr (MT >= 4) {
-    // two m-blocks (97-192 rows) come with 4-6 tiles each
-    if (gemm_mw(g.M) == 2 && epi != EPI_PARTIAL) {
-      dim3 grid((g.N / 128) * cdiv_i(g.M, MT * 32), splits, 1);
-      if (epi == EPI_ARGMAX && g.kper == 64 * KS) k_gemm_x2<MT, 64, EPI_ARGMAX><<<grid, 512, 0, st>>>(g);
-      else if (epi == EPI_ARGMAX) k_gemm_x2<MT, 0, EPI_ARGMAX><<<grid, 512, 0, st>>>(g);
-      else if (g.kper == 64 * KS) k_gemm_x2c<2 * MT, 64, EPI_SWIGLU, true><<<grid, 512, 0, st>>>(g);
-      else k_gemm_x2<MT, 0, EPI_SWIGLU><<<grid, 512, 0, st>>>(g);
-      return;
-    }
-  }
-  // one m-block (at most 6 tiles: every m-tile count below 4 is one)
-  const bool single = MT < 4 || g.M <= MT * 16;
+  dim3 grid(g.N / 128, splits, 1);
+  const int steps = g.kper / KS;
+  const bool exact = (int64_t)g.kper * splits == g.K;
   if (epi == EPI_ARGMAX) {
-    dim3 grid((g.N / 128) * cdiv_i(g.M, MT * 16), splits, 1);
-    if (single && g.kper == 64 * KS) k_gemm<MT, 64, EPI_ARGMAX, 1, true><<<grid, 256, 0, st>>>(g);
-    else if (single) k_gemm<MT, 0, EPI_ARGMAX, 1, true><<<grid, 256, 0, st>>>(g);
-    else if (g.kper == 64 * KS) k_gemm<MT, 64, EPI_ARGMAX, 1><<<grid, 256, 0, st>>>(g);
-    else k_gemm<MT, 0, EPI_ARGMAX, 1><<<grid, 256, 0, st>>>(g);
-  } else if (gemm_mw(g.M) == 2) {
-    if constexpr (MT >= 4) {
-      const int steps = g.kper / KS;
-      const bool exact = (int64_t)g.kper * splits == g.K;
-      dim3 grid((g.N / 128) * cdiv_i(g.M, MT * 32), splits, 1);
-      if (exact && steps == 8) { k_gemm_x2c<2 * MT, 8, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g); return; }
-      if (exact && steps == 16) { k_gemm_x2c<2 * MT, 16, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g); return; }
-      if (exact && steps == 32) { k_gemm_x2c<2 * MT, 32, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g); return; }
-      if (exact && steps == 48) { k_gemm_x2c<2 * MT, 48, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g); return; }
-      if (exact && steps == 64) { k_gemm_x2c<2 * MT, 64, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g); return; }
-    }
-    launch_mw<MT, 2, false>(g, epi, splits, st);
-  } else if (single) {
-    launch_mw<MT, 1, true>(g, epi, splits, st);
+    if (steps == 64) k_gemm<MT, 64, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
+    else k_gemm<MT, 0, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
+  } else if (epi == EPI_SWIGLU) {
+    if (steps == 64) k_gemm<MT, 64, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
+    else k_gemm<MT, 0, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 4) {
+    k_gemm<MT, 4, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 8) {
+    k_gemm<MT, 8, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 12) {
+    k_gemm<MT, 12, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 16) {
+    k_gemm<MT, 16, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 32) {
+    k_gemm<MT, 32, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 48) {
+    k_gemm<MT, 48, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
   } else {
-    launch_mw<MT, 1, false>(g, epi, splits, st);
+    k_gemm<MT, 0, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
   }
 }
 
@@ -809,19 +474,6 @@ void launch_pack_weights(const bf16_t* W, const bf16_t* W2, int N, int K, bf16_t
   k_pack_weights<<<blocks, 256, 0, st>>>(W, W2, K, chunks, reinterpret_cast<uint4*>(dst), N / 128);
 }
 
-// 16-row tiles per m-block: up to 6 (96 rows); more rows take more m-blocks
-int gemm_mt(int M) {
-  const int t = std::max(1, cdiv_i(M, 16));
-  if (t <= 6) return t;
-  return cdiv_i(t, cdiv_i(t, 6));  // balanced m-blocks of at most 6 tiles
-}
-
-// m-blocks per workgroup: 2 when the rows make exactly two m-blocks
-int gemm_mw(int M) { return cdiv_i(M, 16 * gemm_mt(M)) == 2 ? 2 : 1; }
-
-// workgroups per 128-column block and split
-int gemm_mblock_groups(int M) { return cdiv_i(M, 16 * gemm_mt(M) * gemm_mw(M)); }
-
 // 33-64 rows: the column-quarter kernel with four m-tiles (its 64-row tile
 // then holds the rows exactly), for SwiGLU and exact splits of 8-64 k-steps.
 // At 64 rows qkv 13.1 -> 12.1 us, o 10.3 -> 9.5, gate/up 38.4 -> 37.8, down
@@ -829,20 +481,20 @@ int gemm_mblock_groups(int M) { return cdiv_i(M, 16 * gemm_mt(M) * gemm_mw(M)); 
 bool launch_x2c_64(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   const int steps = g.kper / KS;
   if ((int64_t)g.kper * splits != g.K) return false;
-  dim3 grid((g.N / 128) * cdiv_i(g.M, 64), splits, 1);
+  dim3 grid(g.N / 128, splits, 1);
   if (epi == EPI_SWIGLU) {
     if (steps != 64) return false;
-    k_gemm_x2c<4, 64, EPI_SWIGLU, true><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<4, 64, EPI_SWIGLU><<<grid, 512, 0, st>>>(g);
   } else if (steps == 8) {
-    k_gemm_x2c<4, 8, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<4, 8, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 16) {
-    k_gemm_x2c<4, 16, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<4, 16, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 32) {
-    k_gemm_x2c<4, 32, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<4, 32, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 48) {
-    k_gemm_x2c<4, 48, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<4, 48, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 64) {
-    k_gemm_x2c<4, 64, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<4, 64, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else {
     return false;
   }
@@ -856,11 +508,11 @@ bool launch_x2c_64(const GemmArgs& g, int epi, int splits, hipStream_t st) {
 bool launch_x2c_80(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   const int steps = g.kper / KS;
   if (epi != EPI_PARTIAL || (int64_t)g.kper * splits != g.K) return false;
-  dim3 grid((g.N / 128) * cdiv_i(g.M, 80), splits, 1);
+  dim3 grid(g.N / 128, splits, 1);
   if (steps == 8) {
-    k_gemm_x2c<5, 8, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<5, 8, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 16) {
-    k_gemm_x2c<5, 16, EPI_PARTIAL, true><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<5, 16, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else {
     return false;
   }
@@ -870,12 +522,11 @@ bool launch_x2c_80(const GemmArgs& g, int epi, int splits, hipStream_t st) {
 void launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   if (g.M > 32 && g.M <= 64 && epi != EPI_ARGMAX && launch_x2c_64(g, epi, splits, st)) return;
   if (g.M > 64 && g.M <= 80 && launch_x2c_80(g, epi, splits, st)) return;
-  switch (gemm_mt(g.M)) {
+  switch (cdiv_i(g.M, 16)) {
     case 1: launch_mt<1>(g, epi, splits, st); break;
     case 2: launch_mt<2>(g, epi, splits, st); break;
     case 3: launch_mt<3>(g, epi, splits, st); break;
     case 4: launch_mt<4>(g, epi, splits, st); break;
-    case 5: launch_mt<5>(g, epi, splits, st); break;
-    default: launch_mt<6>(g, epi, splits, st); break;  // gemm_mt never exceeds 6
+    default: launch_mt<5>(g, epi, splits, st); break;  // at most kTileRows rows
   }
 }

@@ -102,11 +102,17 @@ void launch_kv_load(const PoolDev& p, const KvGeom& g, int seq, int layer, int p
                     const bf16_t* src, hipStream_t st);
 void launch_add_ctx(int n, int32_t* ctx, const int32_t* add, hipStream_t st);
 
-// GEMM (gemm.hip)
-int gemm_mt(int M);             // 16-row tiles per m-block for M rows
-int gemm_mw(int M);             // m-blocks per workgroup
-int gemm_mblock_groups(int M);  // workgroups per 128-column block and split
+// GEMM of at most kTileRows rows (gemm.hip)
+constexpr int kTileRows = 80;
 void launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t st);
+// GEMM over tiles in LDS, for more than kTileRows rows (gemm_tile.hip): the tile
+// shape, splits and k range a split that suit a shape, with the partial sums
+// within cap_elems; shape -1 when none fits.
+struct TilePlan {
+  int shape, splits, kper;
+};
+TilePlan plan_gemm_tile(int M, int N, int K, int epi, int64_t cap_elems);
+void launch_gemm_tile(const GemmArgs& g, int epi, int shape, int splits, hipStream_t st);
 // W [N][K] row-major -> dst in MFMA fragment order; N % 16 == 0, K % 64 == 0
 // Repack [N][K] weights (N % 128 == 0) into the GEMM's grouped fragment order;
 // W2 non-null: W and W2 are the gate and up halves ([N/2][K] each) of a SwiGLU

@@ -353,14 +353,19 @@ struct Timed {
   }
 };
 
-// Split-K: the fewest splits that divide K exactly, give >= 192 workgroups and
-// leave at most 48 steps of 64 per split; the fully unrolled kernels need exact
-// splits.  Fewer splits mean fewer fp32 partial sums to write and to add up
-// afterwards; below ~192 workgroups too few CUs stream W (measured on the
-// 4096- and 6144-wide projections: 192-256 is the optimum); at 512-1024 rows
-// (prefill chunks) splits of 64-192 steps ran 6-25% slower than 32-48.
+// Split-K of the skinny kernels: the fewest splits that divide K exactly, give
+// >= 192 workgroups and leave at most 48 steps of 64 per split; the fully
+// unrolled kernels need exact splits.  Fewer splits mean fewer fp32 partial sums
+// to write and to add up afterwards; below ~192 workgroups too few CUs stream W
+// (measured on the 4096- and 6144-wide projections: 192-256 is the optimum).
+// Beyond kTileRows rows the tile kernel chooses its own splits; this count (over
+// m-blocks of up to 192 rows) then only bounds the partial sums' memory, which
+// the workspace of a step is sized by.
 Split pick_split(int M, int N, int K, int64_t cap_elems) {
-  const int base = (N / 128) * gemm_mblock_groups(M);  // workgroups per split
+  const int tiles = std::max(1, cdiv_i(M, 16));
+  const int mt = tiles <= 6 ? tiles : cdiv_i(tiles, cdiv_i(tiles, 6));  // balanced m-blocks of at most 6 tiles
+  const int mblocks = cdiv_i(M, 16 * mt);
+  const int base = (N / 128) * (mblocks == 2 ? 1 : mblocks);  // workgroups per split
   for (int s = 1; s <= 64; ++s) {
     if (K % (s * 64)) continue;
     if ((int64_t)base * s >= 192 && K / (s * 64) <= 48 && (int64_t)s * M * N <= cap_elems) return {s, K / s};
@@ -384,8 +389,9 @@ int64_t partials_needed(const ModelDims& md, int R) {
 }
 
 // One projection: P[split][M][N] = A x W^T (or the LM-head argmax epilogue).
+// p_cap bounds the partial elements (partials_needed of the pass).
 war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_rows, const bf16_t* Wp,
-                int M, int N, int K, int* splits_out, hipStream_t st, bool argmax = false,
+                int M, int N, int K, int64_t p_cap, int* splits_out, hipStream_t st, bool argmax = false,
                 float* logits = nullptr, bf16_t* swiglu_out = nullptr) {
   GemmArgs g{};
   g.A = A;
@@ -395,14 +401,20 @@ war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_r
   g.M = M;
   g.N = N;
   g.K = K;
+  const bool fuse = swiglu_out != nullptr;
+  const int epi = argmax ? EPI_ARGMAX : fuse ? EPI_SWIGLU : EPI_PARTIAL;
   // the paired gate/up layout is only read by the SwiGLU epilogue: one split
   Split sp{1, K};
-  if (!argmax && !swiglu_out) {
+  TilePlan tp{-1, 1, K};
+  if (M > kTileRows) {
+    tp = plan_gemm_tile(M, N, K, epi, p_cap);
+    sp = {tp.splits, tp.kper};
+  } else if (epi == EPI_PARTIAL) {
     sp = pick_split(M, N, K, kPartialCap);
-    if ((int64_t)sp.s * M * N > w.p_elems) return fail(WAR_ERR_INVALID_ARG, "internal: split-K partials exceed the workspace");
   }
+  if ((M > kTileRows && tp.shape < 0) || (epi == EPI_PARTIAL && (int64_t)sp.s * M * N > w.p_elems))
+    return fail(WAR_ERR_INVALID_ARG, "internal: split-K partials exceed the workspace");
   g.kper = sp.kper;
-  const bool fuse = swiglu_out != nullptr;
   g.out = swiglu_out;
   g.ld_out = N / 2;
   g.P = w.P;
@@ -410,7 +422,8 @@ war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_r
   g.ld_logits = N;
   g.amax_v = w.amax_v;
   g.amax_i = w.amax_i;
-  launch_gemm(g, argmax ? EPI_ARGMAX : fuse ? EPI_SWIGLU : EPI_PARTIAL, sp.s, st);
+  if (M > kTileRows) launch_gemm_tile(g, epi, tp.shape, sp.s, st);
+  else launch_gemm(g, epi, sp.s, st);
   if (splits_out) *splits_out = sp.s;
   return WAR_OK;
 }
@@ -428,6 +441,7 @@ war_status run_layers(war_model* m, const Workspace& w, war_kv_pool* p, int R, c
   const ModelDims& md = m->md;
   const StepMeta meta = w.meta();
   Profiler& pf = m->prof;
+  const int64_t pc = std::min(w.p_elems, partials_needed(md, R));
   {
     Timed t(pf, st, "rope_table");
     launch_rope_table(R, meta.pos, m->inv_freq.as<double>(), md.hd / 2, w.cos_t, w.sin_t, st);
@@ -441,7 +455,7 @@ war_status run_layers(war_model* m, const Workspace& w, war_kv_pool* p, int R, c
     int s = 1;
     {
       Timed t(pf, st, "gemm_qkv");
-      WARCHK(gemm(w, w.u, md.d, nullptr, L.w_qkv, R, md.qkv, md.d, &s, st));
+      WARCHK(gemm(w, w.u, md.d, nullptr, L.w_qkv, R, md.qkv, md.d, pc, &s, st));
     }
     {
       Timed t(pf, st, "qkv_rope_kvwrite");
@@ -460,7 +474,7 @@ war_status run_layers(war_model* m, const Workspace& w, war_kv_pool* p, int R, c
     }
     {
       Timed t(pf, st, "gemm_o");
-      WARCHK(gemm(w, w.o, md.nq * md.hd, nullptr, L.w_o, R, md.d, md.nq * md.hd, &s, st));
+      WARCHK(gemm(w, w.o, md.nq * md.hd, nullptr, L.w_o, R, md.d, md.nq * md.hd, pc, &s, st));
     }
     {
       Timed t(pf, st, "residual_norm");
@@ -468,11 +482,11 @@ war_status run_layers(war_model* m, const Workspace& w, war_kv_pool* p, int R, c
     }
     {
       Timed t(pf, st, "gemm_gate_up_swiglu");
-      WARCHK(gemm(w, w.u, md.d, nullptr, L.w_gate_up, R, 2 * md.F, md.d, &s, st, false, nullptr, w.y));
+      WARCHK(gemm(w, w.u, md.d, nullptr, L.w_gate_up, R, 2 * md.F, md.d, pc, &s, st, false, nullptr, w.y));
     }
     {
       Timed t(pf, st, "gemm_down");
-      WARCHK(gemm(w, w.y, md.F, nullptr, L.w_down, R, md.d, md.F, &s, st));
+      WARCHK(gemm(w, w.y, md.F, nullptr, L.w_down, R, md.d, md.F, pc, &s, st));
     }
     const bf16_t* gnext = l + 1 < m->cfg.n_layers ? m->layers[l + 1].attn_norm : m->final_norm;
     {
@@ -1015,7 +1029,7 @@ war_status verify_impl(war_model* m, war_kv_pool* p, int32_t B, const int32_t* s
     HIPCHK(m->row_out.ensure((size_t)R * 3 * 4));
     {
       Timed t(m->prof, st, "gemm_lm_head");
-      WARCHK(gemm(w, w.u, m->md.d, nullptr, m->w_lm, R, m->md.V, m->md.d, &sdummy, st, true, lg));
+      WARCHK(gemm(w, w.u, m->md.d, nullptr, m->w_lm, R, m->md.V, m->md.d, 0, &sdummy, st, true, lg));
     }
     SampleArgs sa{};
     sa.logits = lg;
@@ -1035,7 +1049,7 @@ war_status verify_impl(war_model* m, war_kv_pool* p, int32_t B, const int32_t* s
   } else {
     {
       Timed t(m->prof, st, "gemm_lm_head_argmax");
-      WARCHK(gemm(w, w.u, m->md.d, nullptr, m->w_lm, R, m->md.V, m->md.d, &sdummy, st, true, logits));
+      WARCHK(gemm(w, w.u, m->md.d, nullptr, m->w_lm, R, m->md.V, m->md.d, 0, &sdummy, st, true, logits));
     }
     Timed t(m->prof, st, "argmax_accept");
     launch_argmax_accept(B, meta.req_ntok, kp1, m->md.V / 128, w.amax_v, w.amax_i, draft_tokens,
@@ -1283,7 +1297,7 @@ war_status war_prefill_append(war_model* m, war_kv_pool* p, int32_t n, const int
       const int nl = (int)last_rows.size();
       HIPCHK(hipMemcpyAsync(w.a_rows, last_rows.data(), nl * 4, hipMemcpyHostToDevice, st));
       int sd;
-      WARCHK(gemm(w, w.u, m->md.d, w.a_rows, m->w_lm, nl, m->md.V, m->md.d, &sd, st, true,
+      WARCHK(gemm(w, w.u, m->md.d, w.a_rows, m->w_lm, nl, m->md.V, m->md.d, 0, &sd, st, true,
                   last_logits ? last_logits + (int64_t)first_seq * m->md.V : nullptr));
       launch_argmax_accept(nl, nullptr, 1, m->md.V / 128, w.amax_v, w.amax_i, nullptr, nullptr, 0, nullptr,
                            next_tokens + first_seq, nullptr, st);

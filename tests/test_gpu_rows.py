@@ -1,0 +1,82 @@
+"""Passes of more than 80 rows (the tiled GEMM, gemm_tile.hip) against the same
+rows in passes of at most 80 (the skinny kernels, which the oracle tests cover
+at full widths): one layer of the 36-layer shapes under a head of 33 128-id
+blocks, so that a 256-column tile ends half empty.  Row counts sit at the edges
+of the row tiles (128, 192, 256) and of the first row count that takes them.
+Both sides sum in fp32 over the same bf16 rounding points: they differ where a
+value falls on the other side of a rounding, within the bound the oracle
+comparison uses for up to two layers (5e-2 on the logits, 3e-2 on K and V)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2607_17299_amd import harness, synth
+from parity import LOGIT_TOL
+
+pytestmark = pytest.mark.gpu
+CFG = synth.reduced(synth.LARGE, 1, vocab=33 * 128)
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def models():
+    from paper_2607_17299_amd import war
+    w = harness.large_weights(CFG)
+    return {"war": war, "many": war.Model(CFG, w, max_rows=1024), "few": war.Model(CFG, w, max_rows=80)}
+
+
+def _t(a):
+    return torch.as_tensor(np.asarray(a), dtype=torch.int32).to(DEV)
+
+
+@pytest.mark.parametrize("rows", [81, 96, 128, 129, 192, 193, 257, 513, 1000])
+def test_append_rows_match_small_passes(models, rows):
+    war = models["war"]
+    lens = [rows - rows // 3, rows // 3]                 # two sequences share the passes
+    toks = np.concatenate([synth.uniform_tokens(40 + i, n, CFG.vocab) for i, n in enumerate(lens)])
+    out = {}
+    for name in ("many", "few"):
+        pool = war.Pool(CFG, 2 * (rows // 16 + 2), 2, rows // 16 + 2)
+        pool.kv.zero_()
+        logits = torch.zeros((2, CFG.vocab), device=DEV)
+        war.prefill_append(models[name], pool, _t([0, 1]), _t([0, 0]), lens, _t(toks), _t([0, 0]), logits)
+        torch.cuda.synchronize()
+        out[name] = (logits, [pool.gather_kv(s, n, 0).float() for s, n in enumerate(lens)])
+    assert (out["many"][0] - out["few"][0]).abs().max() <= LOGIT_TOL
+    for a, b in zip(out["many"][1], out["few"][1]):
+        assert torch.allclose(a, b, atol=3e-2, rtol=2e-2)
+
+
+@pytest.mark.parametrize("B,k", [(27, 2), (43, 2), (64, 2), (65, 2), (128, 1), (171, 2)])
+def test_verify_rows_match_small_steps(models, B, k):
+    """B * (k + 1) = 81 .. 513 rows, against steps of at most 20 requests."""
+    war = models["war"]
+    pool = war.Pool(CFG, B * 4, B, 4)
+    ctx = [3 + (5 * b) % 37 for b in range(B)]
+    harness.load_contexts(pool, CFG, ctx, list(range(B)), kv_seed=3)
+    rng = np.random.default_rng(B)
+    last, drafts = rng.integers(0, CFG.vocab, B), rng.integers(0, CFG.vocab, (B, k))
+
+    def step(model, lo, hi):
+        n = hi - lo
+        acc, nxt = _t([0] * n), _t([0] * n)
+        logits = torch.zeros((n * (k + 1), CFG.vocab), device=DEV)
+        war.verify_step(model, pool, _t(range(lo, hi)), _t(ctx[lo:hi]), _t(last[lo:hi]), _t(drafts[lo:hi]), None, k,
+                        acc, nxt, logits)
+        war.kv_commit(pool, _t(range(lo, hi)), _t(ctx[lo:hi]), _t([-1] * n))
+        torch.cuda.synchronize()
+        return logits, acc, nxt
+
+    big = step(models["many"], 0, B)
+    small = [step(models["few"], lo, min(B, lo + 20)) for lo in range(0, B, 20)]
+    ref = torch.cat([s[0] for s in small])
+    err = (big[0] - ref).abs().amax(1)
+    assert err.max() <= LOGIT_TOL
+    # the fused argmax is the argmax of the logits it wrote, lowest id first
+    rows = big[0].view(B, k + 1, -1)
+    greedy = (rows == rows.amax(-1, keepdim=True)).int().argmax(-1).cpu().numpy()
+    for b in range(B):
+        a = 0
+        while a < k and drafts[b][a] == greedy[b, a]:
+            a += 1
+        assert (int(big[1][b]), int(big[2][b])) == (a, greedy[b, a])
