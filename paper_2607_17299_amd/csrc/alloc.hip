@@ -112,6 +112,8 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
   __shared__ int s_lead[kBT], s_np[kBT], s_mis[kBT];
   constexpr int kHash = 2 * kBT;  // open-addressing table of the step's ids
   __shared__ int s_hash[kHash];
+  constexpr int kChunks = 5, kMinChunk = 128;  // chunk lengths 2, 1, 1/2, 1/4 and 1/8 of a.chunk
+  __shared__ int s_cnt[kChunks];
   const int t = threadIdx.x;
   const int kp1 = a.k_max + 1;
   __shared__ int s_bad, s_dup;
@@ -120,7 +122,7 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
     s_dup = 0;
   }
   // the attention launches of this step start their work counters at zero
-  if (t < 8) a.unit_ctr[t] = 0;
+  if (t < 8) a.unit_ctr[t * kCtrStride] = 0;
   for (int i = t; i < kHash; i += kBT) s_hash[i] = -1;
   __syncthreads();
   int s = 0, need = 0, ctx = 0, dl = 0, hb = 0;
@@ -180,10 +182,21 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
   // Longer chunks mean fewer partials to write and merge and fewer unit
   // changes; they are used when the batch still has enough items for the grid
   // and no sequences share pages (siblings that read a shared chunk at the same
-  // time find it in L2 more often when the chunks are short).
-  int n2;
-  (void)block_excl_scan((t < a.B && !fail) ? cdiv_i(ctx + dl + 1, 2 * a.chunk) : 0, sh, &n2);
-  const int chunk = n2 >= a.items_double && !a.cascade ? 2 * a.chunk : a.chunk;
+  // time find it in L2 more often when the chunks are short).  A step too small
+  // for the grid takes shorter chunks, down to one 32-key block a wave, while its
+  // units are no more than fill the grid; where every request fits one chunk
+  // nothing is cut (and nothing has to be merged).
+  if (t < kChunks) s_cnt[t] = 0;
+  __syncthreads();
+  if (t < a.B && !fail)
+    for (int c = 0; c < kChunks; ++c) atomicAdd(&s_cnt[c], cdiv_i(ctx + dl + 1, max((2 * a.chunk) >> c, kMinChunk)));
+  __syncthreads();
+  int chunk = a.chunk;
+  if (!a.cascade) {
+    if (s_cnt[0] >= a.items_double) chunk = 2 * a.chunk;
+    else if (s_cnt[1] > a.B)
+      for (int c = 2; c < kChunks && chunk > kMinChunk && s_cnt[c] <= a.items_fill; ++c) chunk >>= 1;
+  }
   const int nch = (t < a.B && !fail) ? cdiv_i(ctx + dl + 1, chunk) : 0;
   int n_items;
   const int ioff = block_excl_scan(nch, sh, &n_items);

@@ -33,11 +33,15 @@ __host__ __device__ inline int key_elem(int s, int d, int head_dim) {
   return ((t * (head_dim >> 5) + (d >> 5)) * 8 + s8) * 32 + (d & 31);
 }
 
+// The attention's eight work counters are a 128-byte line apart (in ints).
+constexpr int kCtrStride = 32;
+
 struct VerifySetupArgs {
   int B, k_max, vocab;
-  int32_t* unit_ctr;  // attention work counters [8], cleared here
+  int32_t* unit_ctr;  // attention work counters, cleared here
   int chunk;         // keys per attention item; doubled when that still leaves
-  int items_double;  // at least this many items (enough to fill the attention grid)
+  int items_double;  // at least this many items (enough to fill the attention grid),
+  int items_fill;    // halved while that leaves at most this many
   int G;        // query heads per kv-head
   int rb;       // attention row block of the step (rows per unit)
   int cascade;  // 1: plan shared-prefix attention units for forked siblings
@@ -84,7 +88,7 @@ struct AttnArgs {
   float* pl;         // [item][kvh][RB]
   float* po;         // [item][kvh][RB][head_dim]
   bf16_t* o;         // combine output [rows][n_q_heads * head_dim]
-  int32_t* unit_ctr; // [8] attention work counters; zero before each attention
+  int32_t* unit_ctr; // attention work counters; zero before each attention
                      // launch (the combine kernel resets them)
 };
 

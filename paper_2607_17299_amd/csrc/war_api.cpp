@@ -90,6 +90,10 @@ constexpr int kPrefillChunk = 4096;  // keys per attention item when prefilling 
 constexpr int kPrefillRows = 128;    // attention rows per prefill row block (k_attn_rows)
 constexpr int kMaxItemsPerSeq = 512;  // attention chunks one combine merges
 constexpr int kAttnGrid = 512;        // persistent attention grid: 2 workgroups per CU
+// Units that a step too small for the grid is cut into.  One request at 8192
+// tokens (8 kv-heads): 72 units of 1024 keys 19.2 us, 264 of 256 11.4 and 520 of
+// 128 13.6; 11 requests at 3000 (4 kv-heads) 132 units 19.3 us, 264 15.6, 528 16.0.
+constexpr int kAttnFill = 512;
 constexpr int64_t kPartialCap = int64_t(64) << 20;  // fp32 split-K partial elements
 
 // Everything a forward pass's kernels use besides the caller's arrays and the
@@ -113,8 +117,8 @@ struct Workspace {
   int32_t* reqs;                 // seq, pos0, ntok, row0 [4][n_req_cap]
   int32_t* segs;                 // begin, count, req, rb [4][n_seg_cap]
   int32_t* n_items;              // [4]
-  int32_t* unit_ctr;             // [8], zero between attention launches
-  int32_t* a_rows;               // [kMaxBatch] LM-head rows of a prefill chunk
+  int32_t* unit_ctr;             // eight, kCtrStride apart, zero between attention launches
+  int32_t* a_rows;               // LM-head rows of a prefill chunk: over the row tokens, which are read by then
   int4* items;                   // [items_cap]
   int4* udesc;                   // [2 * items_cap]
   int32_t* order;                // [items_cap]
@@ -175,12 +179,12 @@ size_t ws_layout(const ModelDims& md, int R, int64_t items, int rb, int64_t p_el
   v.amax_v = reinterpret_cast<float*>(take((size_t)R * nb * 4));
   v.amax_i = reinterpret_cast<int32_t*>(take((size_t)R * nb * 4));
   v.rows = reinterpret_cast<int32_t*>(take((size_t)4 * R * 4));
+  v.a_rows = v.rows;
   v.tree = reinterpret_cast<int32_t*>(take((size_t)2 * R * 4));
   v.reqs = reinterpret_cast<int32_t*>(take((size_t)4 * v.n_req_cap * 4));
   v.segs = reinterpret_cast<int32_t*>(take((size_t)4 * v.n_seg_cap * 4));
   v.n_items = reinterpret_cast<int32_t*>(take(16));
-  v.unit_ctr = reinterpret_cast<int32_t*>(take(8 * 4));
-  v.a_rows = reinterpret_cast<int32_t*>(take((size_t)kMaxBatch * 4));
+  v.unit_ctr = reinterpret_cast<int32_t*>(take(8 * kCtrStride * 4));
   v.items = reinterpret_cast<int4*>(take((size_t)v.items_cap * sizeof(int4)));
   v.udesc = reinterpret_cast<int4*>(take((size_t)v.items_cap * 2 * sizeof(int4)));
   v.order = reinterpret_cast<int32_t*>(take((size_t)v.items_cap * 4));
@@ -532,7 +536,7 @@ war_status ensure_ws(war_model* m, int64_t n_items, int RB) {
   HIPCHK(m->ws_buf.ensure(bytes));
   ws_layout(m->md, m->max_rows, items, rb, pel, m->ws_buf.as<char>(), &w);
   w.tree_step = tree;
-  HIPCHK(hipMemset(w.unit_ctr, 0, 8 * 4));
+  HIPCHK(hipMemset(w.unit_ctr, 0, 8 * kCtrStride * 4));
   return WAR_OK;
 }
 
@@ -935,12 +939,19 @@ war_status verify_impl(war_model* m, war_kv_pool* p, int32_t B, const int32_t* s
   int chunk = 1024;
   while (cdiv_i(p->dev.max_pages * P, chunk) > kMaxItemsPerSeq) chunk *= 2;
   int64_t max_items = (int64_t)B * cdiv_i(p->dev.max_pages * P, chunk);
+  // a step with few keys takes shorter chunks, up to this many items
+  int items_fill = std::min<int64_t>(std::min(kMaxItemsPerSeq, cdiv_i(kAttnFill, m->md.nkv)),
+                                     (int64_t)B * cdiv_i(p->dev.max_pages * P, 128));
   Workspace wsv;
   if (fixed) {
     // a fixed region: rows exactly R; the attention items bound shrinks by
     // longer chunks until the layout fits (the step setup may still double it)
     const int64_t pel = partials_needed(m->md, R);
-    size_t bytes = ws_layout(m->md, R, max_items, RB, pel, nullptr, nullptr);
+    size_t bytes = ws_layout(m->md, R, std::max<int64_t>(max_items, items_fill), RB, pel, nullptr, nullptr);
+    if (bytes > fixed->bytes) {
+      items_fill = 0;
+      bytes = ws_layout(m->md, R, max_items, RB, pel, nullptr, nullptr);
+    }
     while (bytes > fixed->bytes && chunk < (1 << 20)) {
       chunk *= 2;
       max_items = (int64_t)B * cdiv_i(p->dev.max_pages * P, chunk);
@@ -950,8 +961,10 @@ war_status verify_impl(war_model* m, war_kv_pool* p, int32_t B, const int32_t* s
       return fail(WAR_ERR_UNSUPPORTED, "the step's workspace (" + std::to_string(bytes) +
                                            " bytes) exceeds the static scratch (" +
                                            std::to_string(fixed->bytes) + " bytes)");
+    max_items = std::max<int64_t>(max_items, items_fill);
     ws_layout(m->md, R, max_items, RB, pel, fixed->base, &wsv);
   } else {
+    max_items = std::max<int64_t>(max_items, items_fill);
     war_status s = ensure_ws(m, max_items, RB);
     if (s != WAR_OK) return s;
     wsv = m->ws;
@@ -993,6 +1006,7 @@ war_status verify_impl(war_model* m, war_kv_pool* p, int32_t B, const int32_t* s
   va.unit_ctr = w.unit_ctr;
   va.chunk = chunk;
   va.items_double = cdiv_i(2 * kAttnGrid, m->md.nkv);  // 2+ units per workgroup of a full grid
+  va.items_fill = items_fill;
   va.seq_ids = seq_ids;
   va.ctx_lens = ctx_lens;
   va.last_tokens = last_tokens;

@@ -1,0 +1,66 @@
+"""How a verify step cuts its keys into attention units: a step too small for
+the grid takes chunks of 512, 256 or 128 keys, which must give what 1024-key
+chunks give (those the oracle tests cover).  A pool with forked sequences keeps
+1024-key chunks, so the same step runs there as the reference.  Both merge fp32
+partials of the same bf16 products; they differ where a value falls on the other
+side of a rounding, within the bound the oracle comparison uses."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2607_17299_amd import harness, synth
+from parity import LOGIT_TOL
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _t(a):
+    return torch.as_tensor(np.asarray(a), dtype=torch.int32).to(DEV)
+
+
+@pytest.fixture(scope="module")
+def models():
+    from paper_2607_17299_amd import war
+    out = {}
+    for name, cfg in (("large", synth.reduced(synth.LARGE, 1, vocab=1024)), ("tiny", synth.TINY)):
+        if name == "large":
+            w = harness.large_weights(cfg)
+        else:
+            w = {k: v.to(DEV) for k, v in synth.model_weights(cfg, seed=0, norm_std=0.1).items()}
+        out[name] = (cfg, war.Model(cfg, w, max_rows=256))
+    return war, out
+
+
+# (shape, contexts, drafts, keys per item); 8 kv-heads fill at 64 items, 2 at 256
+@pytest.mark.parametrize("shape,ctx,k,chunk", [
+    ("large", [1023], 0, 1024), ("large", [1024], 0, 128), ("large", [1500], 11, 128), ("large", [8191], 0, 128),
+    ("large", [8192], 0, 256), ("large", [16384], 4, 512), ("large", [3000, 17, 1], 8, 128),
+    ("large", [4000] * 7, 3, 512), ("large", [9000] * 7, 2, 1024),
+    ("tiny", [512, 505, 498], 4, 1024), ("tiny", [1030, 3], 23, 128), ("tiny", [5000] * 9, 5, 256)])
+def test_short_chunks_match_whole_ones(models, shape, ctx, k, chunk):
+    war, by_name = models
+    cfg, model = by_name[shape]
+    B = len(ctx)
+    rng = np.random.default_rng(B + k)
+    last, drafts = rng.integers(0, cfg.vocab, B), rng.integers(0, cfg.vocab, (B, max(k, 1)))
+    got = {}
+    for forked in (False, True):
+        pool = war.Pool(cfg, sum(c // 16 + 4 for c in ctx) + 4, B + 3, max(ctx) // 16 + 8)
+        harness.load_contexts(pool, cfg, ctx, list(range(B)), kv_seed=9)
+        seqs, lens, pend, dr = list(range(B)), list(ctx), list(last), list(drafts)
+        if forked:                  # two spare sequences sharing a page, and a batch of two or more
+            pool.alloc([B], [16])
+            pool.fork(B, B + 1, 16)
+            if B == 1:
+                seqs, lens, pend, dr = [0, B + 2], [ctx[0], 0], [last[0], 0], [drafts[0], drafts[0]]
+        n = len(seqs)
+        acc, nxt = _t([0] * n), _t([0] * n)
+        logits = torch.zeros((n * (k + 1), cfg.vocab), device=DEV)
+        war.verify_step(model, pool, _t(seqs), _t(lens), _t(pend), _t(np.stack(dr)), None, k, acc, nxt, logits)
+        torch.cuda.synchronize()
+        keys = war.debug_workspace(model, "n_items", torch.int32, (4,)).cpu().tolist()[3]
+        assert keys == (1024 if forked else chunk)
+        got[forked] = logits[:B * (k + 1)]
+    assert torch.isfinite(got[False]).all()
+    assert (got[False] - got[True]).abs().max() <= LOGIT_TOL
