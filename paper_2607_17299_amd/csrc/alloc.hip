@@ -505,6 +505,27 @@ __global__ void k_kv_load(PoolDev p, KvGeom g, int seq, int layer, int pos0, int
   }
 }
 
+// What a prefill-append checks on the host, gathered into one array: a flag per
+// workgroup (a token outside [0, vocab) among its tokens), the free count, then
+// the n ids, context lengths and held page counts (0 for a bad id).
+__global__ void __launch_bounds__(256) k_append_read(PoolDev p, int n, const int32_t* seq_ids, const int32_t* ctx,
+                                                     int64_t total, const int32_t* tokens, int vocab, int32_t* out) {
+  bool bad = false;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x)
+    bad = bad || tokens[i] < 0 || tokens[i] >= vocab;
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x == 0) out[blockIdx.x] = any;
+  if (blockIdx.x != 0) return;
+  int32_t* o = out + gridDim.x;
+  if (threadIdx.x == 0) o[0] = p.scalars[0];
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const int s = seq_ids[i];
+    o[1 + i] = s;
+    o[1 + n + i] = ctx[i];
+    o[1 + 2 * n + i] = s >= 0 && s < p.max_seqs ? p.held[s] : 0;
+  }
+}
+
 // ctx_lens[i] += n_new[i] (prefill bookkeeping, device side).
 __global__ void k_add_ctx(int n, int32_t* ctx, const int32_t* add) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -540,6 +561,10 @@ void launch_kv_load(const PoolDev& p, const KvGeom& g, int seq, int layer, int p
   const int64_t total = (int64_t)2 * g.n_kv_heads * n * g.head_dim;
   const int blocks = (int)std::min<int64_t>((total + 255) / 256, 65536);
   k_kv_load<<<blocks, 256, 0, st>>>(p, g, seq, layer, pos0, n, src);
+}
+void launch_append_read(const PoolDev& p, int n, const int32_t* seq, const int32_t* ctx, int64_t total,
+                        const int32_t* tokens, int vocab, int flags, int32_t* out, hipStream_t st) {
+  k_append_read<<<flags, 256, 0, st>>>(p, n, seq, ctx, total, tokens, vocab, out);
 }
 void launch_add_ctx(int n, int32_t* ctx, const int32_t* add, hipStream_t st) {
   k_add_ctx<<<cdiv_i(n, 256), 256, 0, st>>>(n, ctx, add);

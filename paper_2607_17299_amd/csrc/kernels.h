@@ -104,6 +104,8 @@ void launch_free(const PoolDev& p, int n, const int32_t* seq, hipStream_t st);
 void launch_fork(const PoolDev& p, int src, int dst, int npg, hipStream_t st);
 void launch_kv_load(const PoolDev& p, const KvGeom& g, int seq, int layer, int pos0, int n,
                     const bf16_t* src, hipStream_t st);
+void launch_append_read(const PoolDev& p, int n, const int32_t* seq, const int32_t* ctx, int64_t total,
+                        const int32_t* tokens, int vocab, int flags, int32_t* out, hipStream_t st);
 void launch_add_ctx(int n, int32_t* ctx, const int32_t* add, hipStream_t st);
 
 // GEMM of at most kTileRows rows (gemm.hip)

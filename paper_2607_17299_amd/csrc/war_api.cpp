@@ -118,7 +118,6 @@ struct Workspace {
   int32_t* segs;                 // begin, count, req, rb [4][n_seg_cap]
   int32_t* n_items;              // [4]
   int32_t* unit_ctr;             // eight, kCtrStride apart, zero between attention launches
-  int32_t* a_rows;               // LM-head rows of a prefill chunk: over the row tokens, which are read by then
   int4* items;                   // [items_cap]
   int4* udesc;                   // [2 * items_cap]
   int32_t* order;                // [items_cap]
@@ -179,7 +178,6 @@ size_t ws_layout(const ModelDims& md, int R, int64_t items, int rb, int64_t p_el
   v.amax_v = reinterpret_cast<float*>(take((size_t)R * nb * 4));
   v.amax_i = reinterpret_cast<int32_t*>(take((size_t)R * nb * 4));
   v.rows = reinterpret_cast<int32_t*>(take((size_t)4 * R * 4));
-  v.a_rows = v.rows;
   v.tree = reinterpret_cast<int32_t*>(take((size_t)2 * R * 4));
   v.reqs = reinterpret_cast<int32_t*>(take((size_t)4 * v.n_req_cap * 4));
   v.segs = reinterpret_cast<int32_t*>(take((size_t)4 * v.n_seg_cap * 4));
@@ -244,10 +242,18 @@ struct war_model {
   Workspace ws;     // views into ws_buf
   DevBuf logits_ws, row_out;  // sampled verification: full logits, per-row outcomes
   DevBuf path_ws;             // tree drafts: accepted path when the caller passes none
-  std::vector<int32_t> h_stage;  // host staging for prefill metadata
-  DevBuf stage_dev;              // device copy of per-prefill host arrays
-  int32_t* pinned = nullptr;     // pinned host staging
-  size_t pinned_ints = 0;
+  // prefill: two pinned blocks of host metadata and their device copies (a row
+  // chunk's is filled while the chunk before it runs), and what the append reads
+  // back first
+  struct Stage {
+    int32_t* host = nullptr;
+    size_t host_ints = 0;
+    DevBuf dev;
+    hipEvent_t used = nullptr;  // recorded behind the last kernel that reads it
+  } stage[2];
+  int32_t* back = nullptr;
+  size_t back_ints = 0;
+  DevBuf back_dev;
   Profiler prof;
 };
 
@@ -438,12 +444,12 @@ war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_r
     if (s_ != WAR_OK) return s_;       \
   } while (0)
 
-// The decoder body over `R` rows whose metadata is in w.meta(); the final
+// The decoder body over `R` rows whose metadata is attn_base.meta; the final
 // normalised hidden state ends in w.u.
 war_status run_layers(war_model* m, const Workspace& w, war_kv_pool* p, int R, const AttnArgs& attn_base,
                       int RB, int attn_grid, int n_segs, hipStream_t st) {
   const ModelDims& md = m->md;
-  const StepMeta meta = w.meta();
+  const StepMeta& meta = attn_base.meta;
   Profiler& pf = m->prof;
   const int64_t pc = std::min(w.p_elems, partials_needed(md, R));
   {
@@ -700,9 +706,14 @@ war_status war_model_create(const war_model_config* cfg, const void* const* weig
 
 void war_model_destroy(war_model* m) {
   if (!m) return;
-  for (DevBuf* b : {&m->wts, &m->inv_freq, &m->ws_buf, &m->path_ws, &m->logits_ws, &m->row_out, &m->stage_dev})
+  for (DevBuf* b : {&m->wts, &m->inv_freq, &m->ws_buf, &m->path_ws, &m->logits_ws, &m->row_out, &m->back_dev,
+                    &m->stage[0].dev, &m->stage[1].dev})
     b->release();
-  if (m->pinned) (void)hipHostFree(m->pinned);
+  for (auto& sg : m->stage) {
+    if (sg.host) (void)hipHostFree(sg.host);
+    if (sg.used) (void)hipEventDestroy(sg.used);
+  }
+  if (m->back) (void)hipHostFree(m->back);
   for (hipEvent_t e : m->prof.pool) (void)hipEventDestroy(e);
   delete m;
 }
@@ -1169,38 +1180,31 @@ war_status war_prefill_append(war_model* m, war_kv_pool* p, int32_t n, const int
     total += n_new_host[i];
   }
   CHECK(total <= (int64_t)1 << 30, "too many new tokens");
-  // read ids, lengths and held pages (one synchronisation)
-  std::vector<int32_t> sid(n), ctx(n), held(p->dev.max_seqs), toks(total);
-  HIPCHK(hipMemcpyAsync(toks.data(), new_tokens, total * 4, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(sid.data(), seq_ids, n * 4, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(ctx.data(), ctx_lens, n * 4, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(held.data(), p->dev.held, held.size() * 4, hipMemcpyDeviceToHost, st));
-  int32_t fc;
-  war_status s = read_free_count(p, st, &fc, nullptr);
+  // ids, lengths, held pages, the free count and whether a token is out of range,
+  // gathered on the device and read back at once (one synchronisation)
+  const int flags = (int)std::min<int64_t>(64, (total + 1023) / 1024);
+  HIPCHK(m->back_dev.ensure((size_t)(kMaxBatch * 3 + 65) * 4));
+  HIPCHK(ensure_pinned(m->back, m->back_ints, (size_t)kMaxBatch * 3 + 65));
+  launch_append_read(p->dev, n, seq_ids, ctx_lens, total, new_tokens, m->md.V, flags, m->back_dev.as<int32_t>(), st);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipMemcpyAsync(m->back, m->back_dev.p, (size_t)(flags + 1 + 3 * n) * 4, hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  const int32_t fc = m->back[flags];
+  set_exact_free(p, fc);
+  const int32_t* b0 = m->back + flags + 1;
+  const std::vector<int32_t> sid(b0, b0 + n), ctx(b0 + n, b0 + 2 * n), held(b0 + 2 * n, b0 + 3 * n);
+  war_status s = check_ids(p, n, sid.data());
   if (s != WAR_OK) return s;
-  s = check_ids(p, n, sid.data());
-  if (s != WAR_OK) return s;
-  for (int64_t i = 0; i < total; ++i)
-    CHECK(toks[i] >= 0 && toks[i] < m->md.V, "token id outside [0, vocab)");
+  for (int i = 0; i < flags; ++i) CHECK(!m->back[i], "token id outside [0, vocab)");
   int64_t need = 0;
   for (int i = 0; i < n; ++i) {
     CHECK(ctx[i] >= 0, "negative ctx_len");
-    const int64_t pages = cdiv_i(ctx[i] + n_new_host[i], P);
+    const int64_t pages = ((int64_t)ctx[i] + n_new_host[i] + P - 1) / P;
     CHECK(pages <= p->dev.max_pages, "sequence would exceed max_pages_per_seq");
-    CHECK(ctx[i] <= (int64_t)held[sid[i]] * P, "ctx_len beyond the sequence's pages");
-    need += std::max<int64_t>(0, pages - held[sid[i]]);
+    CHECK(ctx[i] <= (int64_t)held[i] * P, "ctx_len beyond the sequence's pages");
+    need += std::max<int64_t>(0, pages - held[i]);
   }
   if (need > fc) return fail(WAR_ERR_OUT_OF_PAGES, "not enough free KV pages for the new tokens");
-
-  // reserve: targets = ctx + n_new
-  HIPCHK(m->stage_dev.ensure((size_t)n * 4));
-  HIPCHK(ensure_pinned(m->pinned, m->pinned_ints, (size_t)n));
-  std::memcpy(m->pinned, n_new_host, n * 4);
-  int32_t* d_new = m->stage_dev.as<int32_t>();
-  HIPCHK(hipMemcpyAsync(d_new, m->pinned, n * 4, hipMemcpyHostToDevice, st));
-  launch_grow(p->dev, n, seq_ids, ctx_lens, d_new, 1, st);
-  HIPCHK(hipGetLastError());
-  set_exact_free(p, fc - need);
 
   // forward over chunks of at most max_rows packed rows; attention in row
   // blocks of kPrefillRows rows (k_attn_rows)
@@ -1212,29 +1216,30 @@ war_status war_prefill_append(war_model* m, war_kv_pool* p, int32_t n, const int
   std::vector<int64_t> cu(n + 1, 0);
   for (int i = 0; i < n; ++i) cu[i + 1] = cu[i] + n_new_host[i];
   const int R_cap = m->max_rows;
-  for (int64_t r0 = 0; r0 < total; r0 += R_cap) {
+  int slot = 0;
+  for (int64_t r0 = 0; r0 < total; r0 += R_cap, slot ^= 1) {
     const int64_t r1 = std::min<int64_t>(total, r0 + R_cap);
     const int R = (int)(r1 - r0);
     // requests of this chunk
-    std::vector<int32_t> rq_seq, rq_pos0, rq_ntok, rq_row0, rq_idx;
+    std::vector<int32_t> rq_seq, rq_pos0, rq_ntok, rq_row0, last_rows;
+    int first_seq = -1;
     for (int i = 0; i < n; ++i) {
       const int64_t a = std::max<int64_t>(r0, cu[i]), b = std::min<int64_t>(r1, cu[i + 1]);
       if (a >= b) continue;
-      rq_idx.push_back(i);
       rq_seq.push_back(sid[i]);
       rq_pos0.push_back((int32_t)(ctx[i] + (a - cu[i])));
       rq_ntok.push_back((int32_t)(b - a));
       rq_row0.push_back((int32_t)(a - r0));
-    }
-    const int nr = (int)rq_seq.size();
-    std::vector<int32_t> pos(R), act(R, 1), rreq(R);
-    std::vector<int32_t> sg_b, sg_c, sg_r, sg_rb;
-    std::vector<int4> items, udesc;
-    for (int j = 0; j < nr; ++j) {
-      for (int t = 0; t < rq_ntok[j]; ++t) {
-        pos[rq_row0[j] + t] = rq_pos0[j] + t;
-        rreq[rq_row0[j] + t] = j;
+      if (b == cu[i + 1]) {  // the sequence ends inside this chunk: its last row goes to the LM head
+        if (first_seq < 0) first_seq = i;
+        last_rows.push_back((int32_t)(b - 1 - r0));
       }
+    }
+    const int nr = (int)rq_seq.size(), nl = (int)last_rows.size();
+    std::vector<int32_t> sg_b, sg_c, sg_r, sg_rb;
+    std::vector<int4> udesc;
+    int ni = 0;  // attention items
+    for (int j = 0; j < nr; ++j) {
       // items (and so the merge order) row block by row block; the work order
       // chunk by chunk, so that the units reading one key chunk for different
       // row blocks run together and find it in their XCD's L2
@@ -1242,12 +1247,11 @@ war_status war_prefill_append(war_model* m, war_kv_pool* p, int32_t n, const int
       const int seg0 = (int)sg_b.size();
       for (int rb = 0; rb < nrb; ++rb) {
         const int S = rq_pos0[j] + std::min(rq_ntok[j], (rb + 1) * TB);
-        const int nch = cdiv_i(S, chunk);
-        sg_b.push_back((int32_t)items.size());
-        sg_c.push_back(nch);
+        sg_b.push_back(ni);
+        sg_c.push_back(cdiv_i(S, chunk));
         sg_r.push_back(j);
         sg_rb.push_back(rb);
-        for (int c = 0; c < nch; ++c) items.push_back(make_int4(j, rb, c, 0));
+        ni += sg_c.back();
       }
       const int max_nch = sg_c.back();  // the last row block sees the most keys
       for (int c = 0; c < max_nch; ++c)
@@ -1259,69 +1263,89 @@ war_status war_prefill_append(war_model* m, war_kv_pool* p, int32_t n, const int
         }
     }
     const int nseg = (int)sg_b.size();
-    CHECK(nseg <= m->ws.n_seg_cap && nr <= m->ws.n_req_cap, "internal: prefill chunk too fragmented");
-    // previous chunk's kernels read the metadata buffers: wait before overwriting
-    // (and before ensure_ws may reallocate the workspace)
-    HIPCHK(hipStreamSynchronize(st));
-    s = ensure_ws(m, (int64_t)items.size(), RB);
+    CHECK(nseg <= m->max_rows + kMaxBatch && nr <= std::max(m->max_rows, kMaxBatch),
+          "internal: prefill chunk too fragmented");
+    if (ni > m->ws.items_cap || RB > m->ws.rb_cap) HIPCHK(hipStreamSynchronize(st));  // about to be reallocated
+    s = ensure_ws(m, ni, RB);
     if (s != WAR_OK) return s;
     m->ws.tree_step = false;  // prefill rows are a causal chain
     const Workspace& w = m->ws;
-    const StepMeta meta = w.meta();  // after any reallocation
-    auto h2d = [&](void* dst, const void* src, size_t bytes) {
-      return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st);
+
+    // the chunk's metadata in one block, one copy; its slot is free once the
+    // chunk before the last one has run
+    war_model::Stage& sg = m->stage[slot];
+    if (!sg.used) HIPCHK(hipEventCreateWithFlags(&sg.used, hipEventDisableTiming));
+    HIPCHK(hipEventSynchronize(sg.used));
+    const size_t ints = 4 + udesc.size() * 4 + (size_t)3 * R + 4 * nr + 4 * nseg + nl + n;
+    HIPCHK(ensure_pinned(sg.host, sg.host_ints, ints));
+    HIPCHK(sg.dev.ensure(sg.host_ints * 4));
+    size_t at = 0;
+    auto put = [&](const void* src, size_t count) {
+      int32_t* dst = sg.dev.as<int32_t>() + at;
+      std::memcpy(sg.host + at, src, count * 4);
+      at += count;
+      return dst;
     };
-    HIPCHK(h2d(meta.pos, pos.data(), R * 4));
-    HIPCHK(h2d(meta.active, act.data(), R * 4));
-    HIPCHK(h2d(meta.row_req, rreq.data(), R * 4));
-    HIPCHK(hipMemcpyAsync(meta.tok, new_tokens + r0, R * 4, hipMemcpyDeviceToDevice, st));
-    HIPCHK(h2d(meta.req_seq, rq_seq.data(), nr * 4));
-    HIPCHK(h2d(meta.req_pos0, rq_pos0.data(), nr * 4));
-    HIPCHK(h2d(meta.req_ntok, rq_ntok.data(), nr * 4));
-    HIPCHK(h2d(meta.req_row0, rq_row0.data(), nr * 4));
-    HIPCHK(h2d(meta.seg_begin, sg_b.data(), nseg * 4));
-    HIPCHK(h2d(meta.seg_count, sg_c.data(), nseg * 4));
-    HIPCHK(h2d(meta.seg_req, sg_r.data(), nseg * 4));
-    HIPCHK(h2d(meta.seg_rb, sg_rb.data(), nseg * 4));
-    HIPCHK(h2d(meta.items, items.data(), items.size() * sizeof(int4)));
-    HIPCHK(h2d(meta.udesc, udesc.data(), udesc.size() * sizeof(int4)));
-    // prefill: the work order is the item list
-    const int32_t ni4[4] = {(int32_t)items.size(), (int32_t)items.size(), 0, chunk};
-    const int32_t ni = ni4[0];
-    HIPCHK(h2d(meta.n_items, ni4, 16));
-    HIPCHK(hipStreamSynchronize(st));  // host vectors go out of scope below
+    StepMeta meta = w.meta();
+    const int32_t ni4[4] = {ni, ni, 0, chunk};
+    meta.n_items = put(ni4, 4);
+    meta.udesc = reinterpret_cast<int4*>(put(udesc.data(), udesc.size() * 4));
+    int32_t *pos = sg.host + at, *rreq = pos + R, *act = rreq + R;
+    meta.pos = sg.dev.as<int32_t>() + at;
+    meta.row_req = meta.pos + R;
+    meta.active = meta.row_req + R;
+    at += (size_t)3 * R;
+    for (int j = 0; j < nr; ++j)
+      for (int t = 0; t < rq_ntok[j]; ++t) {
+        pos[rq_row0[j] + t] = rq_pos0[j] + t;
+        rreq[rq_row0[j] + t] = j;
+        act[rq_row0[j] + t] = 1;
+      }
+    meta.req_seq = put(rq_seq.data(), nr);
+    meta.req_pos0 = put(rq_pos0.data(), nr);
+    meta.req_ntok = put(rq_ntok.data(), nr);
+    meta.req_row0 = put(rq_row0.data(), nr);
+    meta.seg_begin = put(sg_b.data(), nseg);
+    meta.seg_count = put(sg_c.data(), nseg);
+    meta.seg_req = put(sg_r.data(), nseg);
+    meta.seg_rb = put(sg_rb.data(), nseg);
+    const int32_t* a_rows = put(last_rows.data(), nl);
+    const int32_t* d_new = put(n_new_host, n);
+    meta.tok = const_cast<int32_t*>(new_tokens) + r0;  // read only
+    meta.items = nullptr;   // prefill units are in list order
+    meta.order = nullptr;
+    HIPCHK(hipMemcpyAsync(sg.dev.p, sg.host, at * 4, hipMemcpyHostToDevice, st));
+    if (r0 == 0) {  // reserve: targets = ctx + n_new
+      launch_grow(p->dev, n, seq_ids, ctx_lens, d_new, 1, st);
+      HIPCHK(hipGetLastError());
+      set_exact_free(p, fc - need);
+    }
 
     AttnArgs a = attn_args(m, w, p, TB);
-    a.meta.order = nullptr;  // prefill items run in list order
+    a.meta = meta;
     a.prb = RB;
     const int grid = (int)std::min<int64_t>((int64_t)ni * m->md.nkv, kAttnGrid);
     s = run_layers(m, w, p, R, a, RB, std::max(grid, 1), nseg, st);
-    if (s != WAR_OK) return s;
-    // LM head on the rows that end a sequence inside this chunk
-    std::vector<int32_t> last_rows;
-    int first_seq = -1;
-    for (int j = 0; j < nr; ++j) {
-      const int i = rq_idx[j];
-      if (cu[i + 1] <= r1 && cu[i + 1] > r0) {
-        if (first_seq < 0) first_seq = i;
-        last_rows.push_back((int32_t)(cu[i + 1] - 1 - r0));
-      }
+    if (s != WAR_OK) {
+      (void)hipStreamSynchronize(st);  // the slots' copies
+      return s;
     }
-    if (!last_rows.empty()) {
-      const int nl = (int)last_rows.size();
-      HIPCHK(hipMemcpyAsync(w.a_rows, last_rows.data(), nl * 4, hipMemcpyHostToDevice, st));
+    if (nl > 0) {
       int sd;
-      WARCHK(gemm(w, w.u, m->md.d, w.a_rows, m->w_lm, nl, m->md.V, m->md.d, 0, &sd, st, true,
+      WARCHK(gemm(w, w.u, m->md.d, a_rows, m->w_lm, nl, m->md.V, m->md.d, 0, &sd, st, true,
                   last_logits ? last_logits + (int64_t)first_seq * m->md.V : nullptr));
       launch_argmax_accept(nl, nullptr, 1, m->md.V / 128, w.amax_v, w.amax_i, nullptr, nullptr, 0, nullptr,
                            next_tokens + first_seq, nullptr, st);
       HIPCHK(hipGetLastError());
-      HIPCHK(hipStreamSynchronize(st));  // last_rows goes out of scope
     }
+    if (r1 == total) {
+      launch_add_ctx(n, ctx_lens, d_new, st);
+      HIPCHK(hipGetLastError());
+    }
+    HIPCHK(hipEventRecord(sg.used, st));
   }
-  launch_add_ctx(n, ctx_lens, d_new, st);
-  HIPCHK(hipGetLastError());
-  return read_free_count(p, st, &fc, nullptr);  // waits for the whole append
+  HIPCHK(hipStreamSynchronize(st));  // the whole append
+  return WAR_OK;
 }
 
 war_status war_profile(war_model* m, int32_t enable) {
