@@ -21,41 +21,12 @@
 // -> 19 / 14 / 57 / 33; at 1152 rows 74 / 44 / 249 / 141 -> 53 / 39 / 199 / 98; at
 // 2048 rows 130 / 85 / 477 / 263 -> 93 / 58 / 308 / 153 (1340 TFLOP/s), the matrix
 // pipes busy 70% of the cycles a workgroup is resident.
-#include <type_traits>
-
-#include "kernels.h"
+#include "lds_load.h"
 
 namespace {
 
 constexpr int KS = 64;          // k-step
 constexpr int kThreads = 512;   // 8 waves
-
-// LDS byte address of a __shared__ object
-WAR_DEV uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-
-// One wave's 1 KB from memory straight to LDS: lane l's 16 bytes at rsrc + voff
-// go to LDS byte lds + 16 l; past the descriptor's size they are zero.  Written
-// as asm because the compiler waits for every such load in flight before any
-// LDS read (it cannot tell the stages apart).  There is no output register, and
-// sync() waits for them; m0 has no other user in the kernel.
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-template <bool NT>  // NT: non-temporal
-WAR_DEV void load_lds16(uint32_t lds, int voff, i32x4 rsrc) {
-  if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(lds), "v"(voff), "s"(rsrc)
-                 : "memory");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc)
-                 : "memory");
-}
-WAR_DEV i32x4 make_rsrc(const void* p, int64_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  const uint32_t n = bytes < 0xffffffffLL ? (uint32_t)bytes : 0xffffffffu;
-  return i32x4{__builtin_amdgcn_readfirstlane((int)(uint32_t)a), __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)),
-               (int)n, 0x00020000};
-}
 
 // LPS = loads issued per slot (see below).  WNT: one m-block, so every weight
 // byte is used by one workgroup and its load is non-temporal.
