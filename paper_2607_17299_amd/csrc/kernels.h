@@ -146,6 +146,8 @@ void launch_sample(const SampleArgs& s, int32_t* accept_lens, int32_t* next_toke
 // attention (attn.hip)
 int attn_rows_per_block(int G, int k_rows);  // RB (16, 32 or 48)
 void launch_attn(const AttnArgs& a, int RB, int head_dim, int grid, hipStream_t st);
+// 128-row blocks of a prefill (attn_rows.hip)
+void launch_attn_rows(const AttnArgs& a, int head_dim, int grid, hipStream_t st);
 void launch_attn_combine(const AttnArgs& a, int RB, int head_dim, int n_segs, hipStream_t st);
 
 // elementwise / row kernels (rows.hip)
