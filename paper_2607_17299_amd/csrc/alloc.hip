@@ -2,8 +2,8 @@
 // reserve / commit / rollback / fork / free, and the verify-step setup that
 // reserves draft slots and builds the step's row metadata and attention work list.
 //
-// Every bookkeeping kernel runs as ONE workgroup of 1024 threads, so its effect
-// is a deterministic function of its inputs (no cross-workgroup atomics).
+// Every bookkeeping kernel runs as ONE workgroup, so its effect is a
+// deterministic function of its inputs (no cross-workgroup atomics).
 // Policy: pops for batch entries in ascending order, logical pages ascending;
 // pushes in descending entry order, logical pages descending -- a reserve
 // followed by a discard restores the stack exactly.
@@ -12,27 +12,43 @@
 namespace {
 
 constexpr int kBT = 1024;
+constexpr int kPage = 16;  // tokens per page, the only size there is
+
+// Inclusive scan over the wave (row shifts by 1, 2, 4, 8, then the rows' and the
+// halves' totals), in the VALU; lane 63 holds the sum.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+  return x;
+}
 
 // Exclusive scan of one int per thread over the block; *total receives the sum.
-__device__ int block_excl_scan(int v, int* sh, int* total) {
+// One copy of its code for a kernel's scans: these kernels run once a step from a
+// cold instruction cache, where the bytes of code they touch are what they cost.
+__device__ __attribute__((noinline)) int2 block_scan(int v) {
+  __shared__ int sh[16];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
+  const int x = wave_scan(v);
   __syncthreads();
   if (lane == 63) sh[w] = x;
   __syncthreads();
   int off = 0, tot = 0;
+#pragma unroll 1
   for (int i = 0; i < nw; ++i) {
     if (i < w) off += sh[i];
     tot += sh[i];
   }
-  *total = tot;
   __syncthreads();
-  return off + x - v;
+  return make_int2(off + x - v, tot);
+}
+__device__ __forceinline__ int block_excl_scan(int v, int* total) {
+  const int2 r = block_scan(v);
+  *total = r.y;
+  return r.x;
 }
 
 __global__ void k_pool_init(PoolDev p) {
@@ -58,8 +74,7 @@ __global__ void k_pool_init(PoolDev p) {
 }
 
 // Pop `need` pages for entry (seq s) after `off` earlier pops of this call.
-__device__ void pop_pages(const PoolDev& p, int s, int need, int off, int fc) {
-  const int h = p.held[s];
+__device__ void pop_pages(const PoolDev& p, int s, int h, int need, int off, int fc) {
   int32_t* row = p.table + (int64_t)s * p.max_pages;
   for (int j = 0; j < need; ++j) {
     const int page = p.stack[fc - 1 - (off + j)];
@@ -72,7 +87,6 @@ __device__ void pop_pages(const PoolDev& p, int s, int need, int off, int fc) {
 // mode 1: prefill, targets from ctx + n_new).  One thread per entry, n <= 1024.
 __global__ void __launch_bounds__(kBT) k_grow(PoolDev p, int n, const int32_t* seq_ids,
                                               const int32_t* a, const int32_t* b, int mode) {
-  __shared__ int sh[16];
   __shared__ int s_fail;
   const int t = threadIdx.x;
   int s = 0, need = 0, target = 0;
@@ -83,7 +97,7 @@ __global__ void __launch_bounds__(kBT) k_grow(PoolDev p, int n, const int32_t* s
     need = max(0, target - p.held[s]);
   }
   int total;
-  const int off = block_excl_scan(need, sh, &total);
+  const int off = block_excl_scan(need, &total);
   const int fc = p.scalars[0];
   if (t == 0) s_fail = total > fc;
   __syncthreads();
@@ -92,9 +106,9 @@ __global__ void __launch_bounds__(kBT) k_grow(PoolDev p, int n, const int32_t* s
     return;
   }
   if (t < n) {
-    pop_pages(p, s, need, off, fc);
-    p.held[s] += need;
-    p.base[s] = p.held[s];
+    const int h = p.held[s];
+    pop_pages(p, s, h, need, off, fc);
+    p.held[s] = p.base[s] = h + need;
   }
   __syncthreads();
   if (t == 0) p.scalars[0] = fc - total;
@@ -104,60 +118,78 @@ __global__ void __launch_bounds__(kBT) k_grow(PoolDev p, int n, const int32_t* s
 // then build the padded row layout (row b*(k+1)+i = request b, token i) and the
 // attention work list (one item per `chunk` keys of each request).  With tree
 // drafts (k_max + 1 <= 32) token i is tree node i.
+//
+// Latency bounds it: chains of dependent loads between barriers.  What depends on
+// nothing is loaded first, a request's page comparison and work order are done by
+// a wave, and a small batch runs a small workgroup (64 threads a request, up to
+// 1024).  Four groups of four siblings with 512 shared pages 77 -> 13 us (of a
+// 1.75 ms step), 64 long requests 26 -> 13, 4 requests 10 -> 7.
 __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs a, StepMeta m) {
-  __shared__ int sh[16];
   __shared__ int s_fail;
   __shared__ int s_ctx[kBT], s_dl[kBT];
   __shared__ int s_pg0[kBT], s_nch[kBT], s_seq[kBT], s_shr[kBT], s_noff[kBT], s_run[kBT];
   __shared__ int s_lead[kBT], s_np[kBT], s_mis[kBT];
+  __shared__ int s_ioff[kBT], s_slot0[kBT], s_step[kBT], s_first[kBT], s_last[kBT];
   constexpr int kHash = 2 * kBT;  // open-addressing table of the step's ids
   __shared__ int s_hash[kHash];
-  constexpr int kChunks = 5, kMinChunk = 128;  // chunk lengths 2, 1, 1/2, 1/4 and 1/8 of a.chunk
+  // chunk lengths 2, 1, 1/2, 1/4 and 1/8 of a.chunk, at least 128
+  constexpr int kChunks = 5, kMinShift = 7;
+  auto chunks_of = [](int n, int shift) { return (n + (1 << shift) - 1) >> shift; };
   __shared__ int s_cnt[kChunks];
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, nt = blockDim.x, nw = nt >> 6;
   const int kp1 = a.k_max + 1;
+  const int R = a.B * kp1;
   __shared__ int s_bad, s_dup;
+  const int fc = p.scalars[0];
+  int s = 0, ctx = 0, dl = 0;
+  if (t < a.B) {
+    s = a.seq_ids[t];
+    ctx = a.ctx_lens[t];
+    dl = a.draft_lens ? a.draft_lens[t] : a.k_max;
+  }
+  // token of row t, in case it is live
+  const int row_tok = t >= R ? 0 : t % kp1 == 0 ? a.last_tokens[t / kp1]
+                                                : a.draft_tokens[(int64_t)(t / kp1) * a.k_max + t % kp1 - 1];
+  int hsize = 64;  // a power of two, at least 2 B
+  while (hsize < 2 * a.B) hsize *= 2;
   if (t == 0) {
     s_bad = 0;
     s_dup = 0;
   }
   // the attention launches of this step start their work counters at zero
   if (t < 8) a.unit_ctr[t * kCtrStride] = 0;
-  for (int i = t; i < kHash; i += kBT) s_hash[i] = -1;
+  for (int i = t; i < hsize; i += nt) s_hash[i] = -1;
   __syncthreads();
-  int s = 0, need = 0, ctx = 0, dl = 0, hb = 0;
+  int need = 0, hb = 0, page0 = 0;
   if (t < a.B) {
-    s = a.seq_ids[t];
-    ctx = a.ctx_lens[t];
-    dl = a.draft_lens ? a.draft_lens[t] : a.k_max;
     dl = min(max(dl, 0), a.k_max);
     // a bad id, a negative length or a request beyond its block-table row
     // fails the whole step (no page moves, no row is active)
     if (s < 0 || s >= p.max_seqs || ctx < 0 ||
-        cdiv_i(ctx + dl + 1, p.page_size) > p.max_pages) {
+        cdiv_i(ctx + dl + 1, kPage) > p.max_pages) {
       s = 0;
       ctx = 0;
       atomicOr(&s_bad, 1);
     } else {
       // two entries with one id would pop into the same block-table row:
       // insert the id (linear probing; B <= kBT ids never fill the table)
-      unsigned hsh = ((unsigned)s * 2654435761u) >> 21;
-      for (int probe = 0; probe < kHash; ++probe) {
+      unsigned hsh = (((unsigned)s * 2654435761u) >> 21) & (hsize - 1);
+      for (int probe = 0; probe < hsize; ++probe) {
         const int prev = atomicCAS(&s_hash[hsh], -1, s);
         if (prev == -1) break;
         if (prev == s) {
           atomicOr(&s_dup, 1);
           break;
         }
-        hsh = (hsh + 1) & (kHash - 1);
+        hsh = (hsh + 1) & (hsize - 1);
       }
       hb = p.held[s];
-      need = max(0, cdiv_i(ctx + dl + 1, p.page_size) - hb);
+      page0 = p.table[(int64_t)s * p.max_pages];
+      need = max(0, cdiv_i(ctx + dl + 1, kPage) - hb);
     }
   }
   int total;
-  const int off = block_excl_scan(need, sh, &total);  // (its barriers order the inserts)
-  const int fc = p.scalars[0];
+  const int off = block_excl_scan(need, &total);  // (its barriers order the inserts)
   if (t == 0) {
     s_fail = total > fc || s_bad || s_dup;
     if (s_bad) atomicOr(&p.scalars[1], ERR_BAD_TOKEN);
@@ -167,7 +199,7 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
   const bool fail = s_fail;
   if (t < a.B) {
     if (!fail) {
-      pop_pages(p, s, need, off, fc);
+      pop_pages(p, s, hb, need, off, fc);
       p.held[s] = hb + need;
       p.base[s] = hb;
     }
@@ -188,25 +220,31 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
   // nothing is cut (and nothing has to be merged).
   if (t < kChunks) s_cnt[t] = 0;
   __syncthreads();
-  if (t < a.B && !fail)
-    for (int c = 0; c < kChunks; ++c) atomicAdd(&s_cnt[c], cdiv_i(ctx + dl + 1, max((2 * a.chunk) >> c, kMinChunk)));
+  const int len = (t < a.B && !fail) ? ctx + dl + 1 : 0;
+  int csh = 31 - __clz(a.chunk);  // log2 of the chunk (a power of two)
+  if (w * 64 < a.B)
+    for (int c = 0; c < kChunks; ++c) {
+      const int n = wave_scan(chunks_of(len, max(csh + 1 - c, kMinShift)));
+      if (lane == 63) atomicAdd(&s_cnt[c], n);
+    }
   __syncthreads();
-  int chunk = a.chunk;
   if (!a.cascade) {
-    if (s_cnt[0] >= a.items_double) chunk = 2 * a.chunk;
+    if (s_cnt[0] >= a.items_double) ++csh;
     else if (s_cnt[1] > a.B)
-      for (int c = 2; c < kChunks && chunk > kMinChunk && s_cnt[c] <= a.items_fill; ++c) chunk >>= 1;
+#pragma unroll 1
+      for (int c = 2; c < kChunks && csh > kMinShift && s_cnt[c] <= a.items_fill; ++c) --csh;
   }
-  const int nch = (t < a.B && !fail) ? cdiv_i(ctx + dl + 1, chunk) : 0;
+  const int chunk = 1 << csh;
+  const int nch = chunks_of(len, csh);
   int n_items;
-  const int ioff = block_excl_scan(nch, sh, &n_items);
+  const int ioff = block_excl_scan(nch, &n_items);
   if (t < a.B) {
     m.seg_begin[t] = ioff;
     m.seg_count[t] = nch;
     m.seg_req[t] = t;
     m.seg_rb[t] = 0;
-    for (int c = 0; c < nch; ++c) m.items[ioff + c] = make_int4(t, 0, c, 0);
-    s_pg0[t] = (!fail && ctx > 0) ? p.table[(int64_t)s * p.max_pages] : -1 - t;
+    s_ioff[t] = ioff;
+    s_pg0[t] = (!fail && ctx > 0 && hb > 0) ? page0 : -1 - t;
     s_nch[t] = nch;
     s_seq[t] = s;
     s_shr[t] = 0x7fffffff;
@@ -225,22 +263,36 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
       ++g;
     }
     s_lead[t] = L;
-    s_np[t] = (g > 1 && nch > 0) ? min(s_ctx[t], s_ctx[L]) / p.page_size : -1;
+    s_np[t] = (g > 1 && nch > 0) ? min(s_ctx[t], s_ctx[L]) / kPage : -1;
     s_mis[t] = max(s_np[t], 0);
   }
   __syncthreads();
   // first page (below np) where a member's block table differs from the first
-  // member's: all threads compare one request's pages at a time
-  for (int q = 0; q < a.B; ++q) {
+  // member's: a wave per request, eight pages a lane in flight
+  for (int q = w; q < a.B; q += nw) {
     const int np = s_np[q];
-    if (np <= 0) continue;
+    if (np <= 0 || s_lead[q] == q) continue;
     const int32_t* rb = p.table + (int64_t)s_seq[q] * p.max_pages;
     const int32_t* rl = p.table + (int64_t)s_seq[s_lead[q]] * p.max_pages;
-    for (int c = t; c < np; c += kBT)
-      if (rb[c] != rl[c]) atomicMin(&s_mis[q], c);
+    int mis = np;
+    for (int c0 = lane; c0 < np && mis == np; c0 += 512) {
+      int32_t xb[8], xl[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int c = min(c0 + 64 * u, np - 1);
+        xb[u] = rb[c];
+        xl[u] = rl[c];
+      }
+#pragma unroll
+      for (int u = 7; u >= 0; --u)
+        if (xb[u] != xl[u]) mis = min(mis, c0 + 64 * u);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) mis = min(mis, __shfl_xor(mis, o, 64));
+    if (lane == 0) s_mis[q] = mis;
   }
   __syncthreads();
-  if (t < a.B && s_np[t] >= 0) atomicMin(&s_shr[L], s_mis[t] * p.page_size);
+  if (t < a.B && s_np[t] >= 0) atomicMin(&s_shr[L], s_mis[t] * kPage);
   __syncthreads();
   // Shared-prefix units: the whole attention chunks a group shares are attended
   // once per run of consecutive members whose live rows (G per token) fit one
@@ -264,59 +316,58 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
   }
   __syncthreads();
   int nsc = 0;
-  if (t < a.B && a.cascade && g > 1 && nch > 0 && s_shr[L] >= chunk) nsc = min(s_shr[L] / chunk, nch);
+  if (t < a.B && a.cascade && g > 1 && nch > 0 && s_shr[L] >= chunk) nsc = min(s_shr[L] >> csh, nch);
   const int j = t - L;
   const int run = nsc > 0 ? s_run[t] : 0;  // members of the run this request owns (0: not an owner)
-  if (t < a.B && nsc > 0)
-    for (int c = 0; c < nsc; ++c) m.items[ioff + c].w = run > 0 ? run : -1;
-  const int n_mine = (t < a.B) ? nch - nsc + (run > 0 ? nsc : 0) : 0;
-  int n_units;
-  const int noff = block_excl_scan(n_mine, sh, &n_units);
-  if (t < a.B) s_noff[t] = noff;
   // A batch without forked siblings takes every request's whole chunks first,
   // in request order, then the partial last chunks, longest first: the
   // persistent grid then ends on its shortest units (s_mis is free by now and
   // holds each request's partial length).
-  __shared__ int s_grp;
-  if (t == 0) s_grp = 0;
-  __syncthreads();
-  if (t < a.B && g > 1) s_grp = 1;  // every writer stores 1
-  const int len = (t < a.B && nch > 0) ? ctx + dl + 1 : 0;
-  const int n_whole = len / chunk, rem = len % chunk;
+  const int n_whole = len >> csh, rem = len & (chunk - 1);
   if (t < a.B) s_mis[t] = rem;
+  const bool lpt = !__syncthreads_or(t < a.B && g > 1);
+  // Work order otherwise.  A group without shared units whose members have equal
+  // chunk counts gets its items interleaved chunk-major (the members read a shared
+  // chunk at the same time, so later readers find it in cache); else request
+  // order, a run's shared units first.
+  int n_slots;
+  const int noff = block_excl_scan(lpt ? n_whole : t < a.B ? nch - nsc + (run > 0 ? nsc : 0) : 0, &n_slots);
+  const int n_units = lpt ? n_items : n_slots;
+  if (t < a.B) s_noff[t] = noff;
   __syncthreads();
-  const bool lpt = s_grp == 0;
-  int n_whole_all;
-  const int woff = block_excl_scan(lpt ? n_whole : 0, sh, &n_whole_all);
-  // Work order.  A group without shared units whose members have equal chunk
-  // counts gets its items interleaved chunk-major (the members read a shared
-  // chunk at the same time, so later readers find it in cache); otherwise
-  // request order, a run's shared units first.
-  if (t < a.B && nch > 0) {
-    // slot o of the order gets chunk c of this request (and its descriptor)
-    auto put = [&](int o, int c) {
-      m.order[o] = ioff + c;
-      const int wc = c < nsc ? (run > 0 ? run : -1) : 0;
-      m.udesc[2 * o] = make_int4(ioff + c, t, c, (dl + 1) << 16);  // first token 0, dl + 1 rows' tokens
-      m.udesc[2 * o + 1] = make_int4(wc, s, ctx, t * kp1);
-    };
-    if (lpt) {
-      for (int c = 0; c < n_whole; ++c) put(woff + c, c);
-      if (rem > 0) {
-        int rank = 0;  // partial chunks longer than this one, ties by request
-        for (int q = 0; q < a.B; ++q) {
-          const int rq = s_mis[q];
-          rank += rq > rem || (rq == rem && q < t);
-        }
-        put(n_whole_all + rank, n_whole);
-      }
-    } else if (nsc == 0 && g > 1 && regular) {
-      for (int c = 0; c < nch; ++c) put(s_noff[L] + c * g + j, c);
-    } else {
-      int o = noff;
-      if (run > 0)
-        for (int c = 0; c < nsc; ++c) put(o++, c);
-      for (int c = nsc; c < nch; ++c) put(o++, c);
+  // Chunk c >= first of request t goes to slot slot0 + (c - first) * step, but the
+  // partial last chunk of an unforked batch to slot last.
+  if (t < a.B) {
+    const bool mixed = !lpt && nsc == 0 && g > 1 && regular;
+    s_first[t] = nsc > 0 && run == 0 ? nsc : 0;
+    s_slot0[t] = mixed ? s_noff[L] + j : noff;
+    s_step[t] = mixed ? g : 1;
+    s_last[t] = -1;
+    s_np[t] = nsc;
+    s_run[t] = run;
+  }
+  __syncthreads();
+  if (lpt)
+    for (int q = w; q < a.B; q += nw) {
+      const int rem_q = s_mis[q];
+      if (rem_q == 0) continue;
+      int rank = 0;  // partial chunks longer than this one, ties by request
+      for (int x = lane; x < a.B; x += 64) rank += s_mis[x] > rem_q || (s_mis[x] == rem_q && x < q);
+      rank = wave_scan(rank);
+      if (lane == 63) s_last[q] = n_slots + rank;
+    }
+  __syncthreads();
+  for (int q = w; q < a.B; q += nw) {
+    const int nq = s_nch[q], first = s_first[q], nscq = s_np[q], io = s_ioff[q];
+    const int own = s_run[q] > 0 ? s_run[q] : -1;
+    for (int c = lane; c < nq; c += 64) {
+      const int wc = c < nscq ? own : 0;
+      m.items[io + c] = make_int4(q, 0, c, wc);
+      if (c < first) continue;
+      const int o = c == nq - 1 && s_last[q] >= 0 ? s_last[q] : s_slot0[q] + (c - first) * s_step[q];
+      m.order[o] = io + c;
+      m.udesc[2 * o] = make_int4(io + c, q, c, (s_dl[q] + 1) << 16);  // first token 0, dl + 1 rows' tokens
+      m.udesc[2 * o + 1] = make_int4(wc, s_seq[q], s_ctx[q], q * kp1);
     }
   }
   if (t == 0) {
@@ -330,13 +381,12 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
   }
   __syncthreads();
   // rows: request b's token i sits in row b*(k_max+1)+i
-  const int R = a.B * kp1;
-  for (int r = t; r < R; r += blockDim.x) {
+  for (int r = t; r < R; r += nt) {
     const int b = r / kp1, i = r % kp1;
     const int dlb = s_dl[b];
     const bool act = i <= dlb;
     int tok = 0;
-    if (act) tok = i == 0 ? a.last_tokens[b] : a.draft_tokens[(int64_t)b * a.k_max + i - 1];
+    if (act) tok = r == t ? row_tok : i == 0 ? a.last_tokens[b] : a.draft_tokens[(int64_t)b * a.k_max + i - 1];
     if (tok < 0 || tok >= a.vocab) {
       atomicOr(&p.scalars[1], ERR_BAD_TOKEN);
       tok = 0;
@@ -377,9 +427,17 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
 __global__ void __launch_bounds__(kBT) k_commit(PoolDev p, int B, const int32_t* seq_ids,
                                                 int32_t* ctx_lens, const int32_t* accept,
                                                 uint32_t commit_seq) {
-  __shared__ int sh[16];
   __shared__ int s_skip;
   const int t = threadIdx.x;
+  // entry handled by this thread: descending, as the scan runs
+  const int rt = B - 1 - t;
+  int s = 0, acc0 = 0, ctx = 0;
+  if (t < B) {
+    s = seq_ids[rt];
+    acc0 = accept[rt];
+    ctx = ctx_lens[rt];
+  }
+  const int fc = p.scalars[0];
   if (t == 0) s_skip = p.scalars[2];
   __syncthreads();
   if (s_skip) {
@@ -390,11 +448,9 @@ __global__ void __launch_bounds__(kBT) k_commit(PoolDev p, int B, const int32_t*
     }
     return;
   }
-  const int rt = B - 1 - t;  // entry handled by this thread, so the scan runs descending
-  int s = 0, h = 0, keep = 0, rel = 0, new_ctx = 0;
+  int h = 0, keep = 0, rel = 0, new_ctx = 0;
   bool ok = false;
   if (t < B) {
-    s = seq_ids[rt];
     // the verify step accepted these ids; other ids (a different array than
     // the step's) are flagged and left alone
     ok = s >= 0 && s < p.max_seqs;
@@ -402,16 +458,14 @@ __global__ void __launch_bounds__(kBT) k_commit(PoolDev p, int B, const int32_t*
   }
   if (ok) {
     h = p.held[s];
-    const int ctx = ctx_lens[rt];
     const int cap = h * p.page_size;
-    const int acc = min(max(accept[rt], -1), cap - ctx - 1);
+    const int acc = min(max(acc0, -1), cap - ctx - 1);
     new_ctx = ctx + max(acc, -1) + 1;
     keep = min(h, max(p.base[s], cdiv_i(new_ctx, p.page_size)));
     rel = h - keep;
   }
   int total;
-  const int off = block_excl_scan(rel, sh, &total);
-  const int fc = p.scalars[0];
+  const int off = block_excl_scan(rel, &total);
   if (ok) {
     int32_t* row = p.table + (int64_t)s * p.max_pages;
     for (int j = 0; j < rel; ++j) {
@@ -435,7 +489,6 @@ __global__ void __launch_bounds__(kBT) k_commit(PoolDev p, int B, const int32_t*
 // Free sequences: entries in descending order; within one, logical pages
 // descending; a page is pushed when its count drops to 0.
 __global__ void __launch_bounds__(kBT) k_free(PoolDev p, int n, const int32_t* seq_ids) {
-  __shared__ int sh[16];
   __shared__ int s_fc;
   if (threadIdx.x == 0) s_fc = p.scalars[0];
   __syncthreads();
@@ -451,7 +504,7 @@ __global__ void __launch_bounds__(kBT) k_free(PoolDev p, int n, const int32_t* s
         push = p.refcount[page] == 1;
       }
       int total;
-      const int off = block_excl_scan(push, sh, &total);
+      const int off = block_excl_scan(push, &total);
       const int fc = s_fc;
       if (j >= 0) {
         p.refcount[page] -= 1;
@@ -544,11 +597,11 @@ void launch_grow(const PoolDev& p, int n, const int32_t* seq, const int32_t* a, 
 }
 void launch_verify_setup(const PoolDev& p, const VerifySetupArgs& a, const StepMeta& m,
                          hipStream_t st) {
-  k_verify_setup<<<1, kBT, 0, st>>>(p, a, m);
+  k_verify_setup<<<1, std::min(kBT, 64 * a.B), 0, st>>>(p, a, m);
 }
 void launch_commit(const PoolDev& p, int B, const int32_t* seq, int32_t* ctx, const int32_t* acc,
                    uint32_t commit_seq, hipStream_t st) {
-  k_commit<<<1, kBT, 0, st>>>(p, B, seq, ctx, acc, commit_seq);
+  k_commit<<<1, std::min(kBT, (B + 63) / 64 * 64), 0, st>>>(p, B, seq, ctx, acc, commit_seq);
 }
 void launch_free(const PoolDev& p, int n, const int32_t* seq, hipStream_t st) {
   k_free<<<1, kBT, 0, st>>>(p, n, seq);

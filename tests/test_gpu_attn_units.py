@@ -64,3 +64,57 @@ def test_short_chunks_match_whole_ones(models, shape, ctx, k, chunk):
         got[forked] = logits[:B * (k + 1)]
     assert torch.isfinite(got[False]).all()
     assert (got[False] - got[True]).abs().max() <= LOGIT_TOL
+
+
+def _plan(war, model, pool, lens, k):
+    """Items, work order, units and keys per item of a step over sequences 0 .. B-1."""
+    B = len(lens)
+    acc, nxt = _t([0] * B), _t([0] * B)
+    war.verify_step(model, pool, _t(range(B)), _t(lens), _t([1] * B), _t(np.ones((B, max(k, 1)))), None, k, acc, nxt)
+    war.kv_commit(pool, _t(range(B)), _t(lens), _t([-1] * B))
+    torch.cuda.synchronize()
+    get = lambda name, shape: war.debug_workspace(model, name, torch.int32, shape).cpu().numpy()
+    n_items, n_units, _, chunk = get("n_items", (4,)).tolist()
+    return get("items", (n_items, 4)), get("order", (n_units,)), n_units, chunk
+
+
+@pytest.mark.parametrize("B", [1, 2, 17, 64, 65, 128])
+def test_work_order_of_an_unforked_batch(models, B):
+    """Whole chunks in request order, then the partial ones, longest first."""
+    war, by_name = models
+    cfg, model = by_name["tiny"]
+    rng = np.random.default_rng(B)
+    lens = [int(x) for x in rng.choice([0, 1, 127, 1023, 1024, 2047, 2048, 3000, 4095], B)]
+    pool = war.Pool(cfg, sum(c // 16 + 2 for c in lens), B, 260)
+    pool.kv.zero_()
+    pool.alloc(list(range(B)), lens)
+    items, order, n_units, chunk = _plan(war, model, pool, lens, 0)
+    keys = [n + 1 for n in lens]
+    want = [[b, 0, c, 0] for b, n in enumerate(keys) for c in range(-(-n // chunk))]
+    assert items.tolist() == want and n_units == len(want)
+    whole = [i for i, (b, _, c, _) in enumerate(want) if (c + 1) * chunk <= keys[b]]
+    part = [i for i, (b, _, c, _) in enumerate(want) if (c + 1) * chunk > keys[b]]
+    part.sort(key=lambda i: (-(keys[want[i][0]] % chunk), want[i][0]))
+    assert order.tolist() == whole + part
+
+
+@pytest.mark.parametrize("pages", [1, 63, 64, 65, 127, 511, 512, 513, 576])
+def test_shared_pages_of_forked_siblings(models, pages):
+    """Three siblings with `pages` pages in common and a stranger: the 1024-key
+    chunks inside them are attended once for all three."""
+    war, by_name = models
+    cfg, model = by_name["tiny"]
+    lens = [pages * 16 + 40, pages * 16 + 3, pages * 16 + 200, 700]
+    pool = war.Pool(cfg, 3 * pages + 120, 4, pages + 60)
+    pool.kv.zero_()
+    pool.alloc([0], [lens[0]])
+    for s in (1, 2):
+        pool.fork(0, s, pages * 16)
+    pool.alloc([1, 2, 3], lens[1:])
+    items, order, n_units, chunk = _plan(war, model, pool, lens, 0)
+    shared = pages * 16 // 1024
+    n = [-(-(x + 1) // 1024) for x in lens]
+    assert chunk == 1024 and n_units == sum(n) - 2 * shared
+    own = {0: 3, 1: -1, 2: -1, 3: 0}
+    assert items.tolist() == [[b, 0, c, own[b] if c < shared else 0] for b in range(4) for c in range(n[b])]
+    assert sorted(order.tolist()) == [i for i, it in enumerate(items.tolist()) if it[3] >= 0]
