@@ -424,10 +424,18 @@ void launch_mt(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   const bool exact = (int64_t)g.kper * splits == g.K;
   if (epi == EPI_ARGMAX) {
     if (steps == 64) k_gemm<MT, 64, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
+    else if (steps == 16) k_gemm<MT, 16, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
     else k_gemm<MT, 0, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
   } else if (epi == EPI_SWIGLU) {
     if (steps == 64) k_gemm<MT, 64, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
+    else if (steps == 16) k_gemm<MT, 16, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
     else k_gemm<MT, 0, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 1) {
+    k_gemm<MT, 1, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 2) {
+    k_gemm<MT, 2, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
+  } else if (exact && steps == 24) {
+    k_gemm<MT, 24, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
   } else if (exact && steps == 4) {
     k_gemm<MT, 4, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
   } else if (exact && steps == 8) {
@@ -485,6 +493,8 @@ bool launch_x2c_64(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   if (epi == EPI_SWIGLU) {
     if (steps != 64) return false;
     k_gemm_x2c<4, 64, EPI_SWIGLU><<<grid, 512, 0, st>>>(g);
+  } else if (steps == 24) {
+    k_gemm_x2c<4, 24, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 8) {
     k_gemm_x2c<4, 8, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 16) {
@@ -501,15 +511,17 @@ bool launch_x2c_64(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   return true;
 }
 
-// 65-80 rows: the short split-K projections (splits of 8 and 16 k-steps: qkv
-// and o) take the column-quarter kernel with five m-tiles; at 72 rows qkv and
-// o run 3-4% faster than in k_gemm, while gate/up and the 32-step down
-// projection run 1-4% slower and stay there (weights rotated).
+// 65-80 rows: the short split-K projections (splits of 8, 16 and 24 k-steps: o,
+// qkv and down) take the column-quarter kernel with five m-tiles; at 72 rows qkv
+// and o run 3-4% faster than in k_gemm, while gate/up and splits of 32 steps run
+// 1-4% slower and stay there (weights rotated).
 bool launch_x2c_80(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   const int steps = g.kper / KS;
   if (epi != EPI_PARTIAL || (int64_t)g.kper * splits != g.K) return false;
   dim3 grid(g.N / 128, splits, 1);
-  if (steps == 8) {
+  if (steps == 24) {
+    k_gemm_x2c<5, 24, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
+  } else if (steps == 8) {
     k_gemm_x2c<5, 8, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 16) {
     k_gemm_x2c<5, 16, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);

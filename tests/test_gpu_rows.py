@@ -80,3 +80,31 @@ def test_verify_rows_match_small_steps(models, B, k):
         while a < k and drafts[b][a] == greedy[b, a]:
             a += 1
         assert (int(big[1][b]), int(big[2][b])) == (a, greedy[b, a])
+
+
+# one layer of narrow matrices: splits of one and two k-steps, a residual of more
+# than eight splits over rows of 1024 (four thread groups), 768 (five) and 2048 (two)
+@pytest.mark.parametrize("d,heads,ffn", [(1024, 16, 4096), (768, 12, 3072), (2048, 16, 2048)])
+@pytest.mark.parametrize("B,k", [(1, 0), (4, 3), (11, 2), (8, 5), (11, 5), (16, 4)])
+def test_narrow_matrices_match_oracle(d, heads, ffn, B, k):
+    from oracle.decoder import RequestKV, Weights
+    from oracle.verify import verify_request
+    from paper_2607_17299_amd import war
+    cfg = synth.ModelConfig(n_layers=1, d_model=d, n_q_heads=heads, n_kv_heads=heads // 4, head_dim=64, ffn_dim=ffn,
+                            vocab=1024)
+    w = synth.model_weights(cfg, seed=1, norm_std=0.1)
+    model, W = war.Model(cfg, {n: t.to(DEV) for n, t in w.items()}, max_rows=80), Weights(cfg, w)
+    ctx = [1 + (7 * b) % 23 for b in range(B)]
+    pool = war.Pool(cfg, B * 4, B, 4)
+    harness.load_contexts(pool, cfg, ctx, list(range(B)), kv_seed=4)
+    rng = np.random.default_rng(B + k)
+    last, drafts = rng.integers(0, cfg.vocab, B), rng.integers(0, cfg.vocab, (B, max(k, 1)))
+    acc, nxt = _t([0] * B), _t([0] * B)
+    logits = torch.zeros((B * (k + 1), cfg.vocab), device=DEV)
+    war.verify_step(model, pool, _t(range(B)), _t(ctx), _t(last), _t(drafts), None, k, acc, nxt, logits)
+    torch.cuda.synchronize()
+    got = logits.cpu().numpy().reshape(B, k + 1, -1)
+    for b in range(0, B, 3):
+        kv = synth.kv_context(cfg, 4, b, 0, 0, ctx[b], DEV).cpu().double().numpy()
+        r = verify_request(cfg, W, RequestKV(cfg, [(kv[0], kv[1])]), int(last[b]), drafts[b][:k].tolist())
+        assert np.abs(r["logits"] - got[b]).max() <= LOGIT_TOL
