@@ -156,10 +156,10 @@ struct ModelDims {
   int d, nq, nkv, hd, F, V, qkv;
   float eps;
 };
-void launch_rope_table(int rows, const int32_t* pos, const double* inv_freq, int half, float* cos_t,
-                       float* sin_t, hipStream_t st);
+// embeddings and first norm, and the RoPE table of the pass
 void launch_embed_norm(int rows, const int32_t* tok, const bf16_t* E, const bf16_t* g, int d,
-                       float eps, float* h, bf16_t* u, hipStream_t st);
+                       float eps, float* h, bf16_t* u, const int32_t* pos, const double* inv_freq,
+                       int half, float* cos_t, float* sin_t, hipStream_t st);
 void launch_residual_norm(int rows, int splits, const float* P, int d, const bf16_t* g, float eps,
                           float* h, bf16_t* u, hipStream_t st);
 void launch_qkv_rope(int rows, int splits, const float* P, const ModelDims& md,

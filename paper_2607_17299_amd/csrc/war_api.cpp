@@ -467,12 +467,9 @@ war_status run_layers(war_model* m, const Workspace& w, war_kv_pool* p, int R, c
   Profiler& pf = m->prof;
   const int64_t pc = std::min(w.p_elems, partials_needed(md, R));
   {
-    Timed t(pf, st, "rope_table");
-    launch_rope_table(R, meta.pos, m->inv_freq.as<double>(), md.hd / 2, w.cos_t, w.sin_t, st);
-  }
-  {
     Timed t(pf, st, "embed_norm");
-    launch_embed_norm(R, meta.tok, m->embed, m->layers[0].attn_norm, md.d, md.eps, w.h, w.u, st);
+    launch_embed_norm(R, meta.tok, m->embed, m->layers[0].attn_norm, md.d, md.eps, w.h, w.u, meta.pos,
+                      m->inv_freq.as<double>(), md.hd / 2, w.cos_t, w.sin_t, st);
   }
   for (int l = 0; l < m->cfg.n_layers; ++l) {
     const LayerW& L = m->layers[l];
