@@ -43,7 +43,8 @@
 // wave w of block nb owning gate n-tile 4nb + w and the matching up n-tile,
 // and writes bf16 silu(gate) * up for its 16 columns.  At 33-64 rows SwiGLU and
 // the partial sums of splits of 8-64 k-steps run in k_gemm_x2c (below), which
-// also takes the 8- and 16-step splits at 65-80 rows.
+// also takes the 8-, 16- and 24-step splits at 65-80 rows and gate/up of 256 or
+// fewer 96-column workgroups up to 160 rows.
 #include "kernels.h"
 
 namespace {
