@@ -4,8 +4,8 @@
 // W a weight matrix stored [out][in].  In most verify steps M is 1..80 rows
 // against N x K weights of 16-310 MB, so the kernel is bound by streaming W
 // from HBM: every weight byte is read exactly once.  (More rows run in
-// gemm_tile.hip, but for gate/up up to 160: at 96 rows qkv 14.9 -> 12.5 us, o 11.3 -> 10.2, down 25.2 ->
-// 22.8; at 80 rows qkv is slower there.)
+// gemm_tile.hip: at 96 rows qkv 14.9 -> 12.5 us, o 11.3 -> 10.2, down 25.2 ->
+// 22.8, gate/up 40.7 -> 41; at 80 rows gate/up and qkv are slower there.)
 //
 // Weights are repacked once, when the model is created, into MFMA fragment
 // order: for n-tile nt (16 output rows), k-step s (64 inputs) and half j, the
@@ -43,8 +43,7 @@
 // wave w of block nb owning gate n-tile 4nb + w and the matching up n-tile,
 // and writes bf16 silu(gate) * up for its 16 columns.  At 33-64 rows SwiGLU and
 // the partial sums of splits of 8-64 k-steps run in k_gemm_x2c (below), which
-// also takes the 8-, 16- and 24-step splits at 65-80 rows and gate/up of 256 or
-// fewer 96-column workgroups up to 160 rows.
+// also takes the 8-, 16- and 24-step splits at 65-80 rows.
 #include "kernels.h"
 
 namespace {
@@ -269,52 +268,50 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))
   }
 }
 
-// SwiGLU (one split of 64 k-steps) at 33-160 rows and split-K partial sums at
-// 33-80, column-quarter waves: wave (kh, cq) owns k-half kh of every step and two
-// n-tiles (a gate tile with its up tile, or tiles 2cq, 2cq + 1) for
+// SwiGLU (one split of 64 k-steps) and split-K partial sums at 33-80 rows,
+// column-quarter waves: wave (kh, cq) owns k-half kh of every step and two
+// n-tiles (gate tile cq with its up tile 4 + cq, or tiles 2cq, 2cq + 1) for
 // all RT m-tiles (one A fragment read from LDS feeds two MFMAs), so no
 // two waves load the same weight fragment and every weight byte is used by one
 // workgroup (non-temporal weight loads).  The two k-halves' sums meet in
 // LDS at the end, the kh = 0 waves writing the first ceil(RT/2) m-tiles and
-// the kh = 1 waves the rest.  NQ = 3: three quarters, workgroups of 96 columns.
-template <int RT, int NSTEPS, int EPI, int NQ = 4>
-__global__ void __launch_bounds__(NQ * 128) __attribute__((amdgpu_waves_per_eu(1, 2))) k_gemm_x2c(GemmArgs g) {
+// the kh = 1 waves the rest.
+template <int RT, int NSTEPS, int EPI>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) k_gemm_x2c(GemmArgs g) {
   static_assert(EPI == EPI_SWIGLU || EPI == EPI_PARTIAL, "SwiGLU or partial sums");
-  static_assert(NQ == 4 || EPI == EPI_SWIGLU, "96 columns: gate/up only");
-  constexpr int NT = NQ * 128;
   constexpr int A_CHUNKS = RT * 16 * (KS / 8);
-  constexpr int A_PER = (A_CHUNKS + NT - 1) / NT;
+  constexpr int A_PER = (A_CHUNKS + 511) / 512;
   constexpr int A_BYTES = RT * 16 * ROWB;
   constexpr int LO = (RT + 1) / 2, HI = RT - LO;     // m-tiles the k-half 0 / 1 waves keep
-  constexpr int X_BYTES = NQ * 2 * LO * 2 * 64 * 16;
+  constexpr int X_BYTES = 4 * 2 * LO * 2 * 64 * 16;
   constexpr int S_BYTES = 3 * A_BYTES > X_BYTES ? 3 * A_BYTES : X_BYTES;
   __shared__ __attribute__((aligned(16))) unsigned char smem[S_BYTES];
   auto sA = [&](int buf) { return smem + buf * A_BYTES; };
   const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, lg = lane >> 4;
   const int wi = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kh = wi / NQ, cq = wi % NQ;
+  const int kh = wi >> 2, cq = wi & 3;
   const int nb = blockIdx.x;
   constexpr int m0 = 0;
   const int split = blockIdx.y;
   const int kb = split * g.kper;
   const int s0 = kb / KS;
   const int nsteps = NSTEPS;
-  const int gt = nb * NQ + cq;  // SwiGLU: the wave's gate tile, tile gt % 4 of group gt / 4
-  const bf16_t* Wb = g.Wp + (EPI == EPI_SWIGLU ? 0 : (int64_t)nb * (8 * KS * 16));
+  const int tb = nb * 4;
+  const bf16_t* Wb = g.Wp + (int64_t)nb * (8 * KS * 16);
   const int NG = g.N / 128;
   const __amdgpu_buffer_rsrc_t wres =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(Wb), 0, 0x7fffffff, 0x00020000);
   const __amdgpu_buffer_rsrc_t ares =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(g.A), 0, 0x7fffffff, 0x00020000);
   const int64_t sstride = (int64_t)NG * (KS * 256);
-  // the wave's two tiles: SwiGLU a gate tile and its up tile, else tiles 2cq, 2cq + 1
-  const int t0 = EPI == EPI_SWIGLU ? (gt >> 2) * 8 + (gt & 3) : 2 * cq, t1 = EPI == EPI_SWIGLU ? t0 + 4 : 2 * cq + 1;
+  // the wave's two tiles: SwiGLU gate tile cq and up tile 4 + cq, else tiles 2cq, 2cq + 1
+  const int t0 = EPI == EPI_SWIGLU ? cq : 2 * cq, t1 = EPI == EPI_SWIGLU ? 4 + cq : 2 * cq + 1;
   const int wg0 = (t0 * 2 + kh) * 1024 + lane * 16, wu0 = (t1 * 2 + kh) * 1024 + lane * 16;
   int av[A_PER];
   int aoff[A_PER];
 #pragma unroll
   for (int i = 0; i < A_PER; ++i) {
-    const int c = min(tid + NT * i, A_CHUNKS - 1);
+    const int c = min(tid + 512 * i, A_CHUNKS - 1);
     const int r = c >> 3, q = c & 7;
     const int gm = m0 + r;
     aoff[i] = r * ROWB + q * 16;
@@ -339,7 +336,7 @@ __global__ void __launch_bounds__(NQ * 128) __attribute__((amdgpu_waves_per_eu(1
   auto store_a = [&](const uint4* ar, int buf) {
 #pragma unroll
     for (int i = 0; i < A_PER; ++i)
-      if (A_CHUNKS % NT == 0 || tid + NT * i < A_CHUNKS)
+      if (A_CHUNKS % 512 == 0 || tid + 512 * i < A_CHUNKS)
         *reinterpret_cast<uint4*>(sA(buf) + aoff[i]) = ar[i];
   };
   f32x4 acc[RT][2];
@@ -402,7 +399,7 @@ __global__ void __launch_bounds__(NQ * 128) __attribute__((amdgpu_waves_per_eu(1
       if (m >= g.M) continue;
       if constexpr (EPI == EPI_SWIGLU) {
         const float a = gsum[i];
-        g.out[(int64_t)m * g.ld_out + gt * 16 + ln] = f2bf(a / (1.f + expf(-a)) * usum[i]);
+        g.out[(int64_t)m * g.ld_out + (tb + cq) * 16 + ln] = f2bf(a / (1.f + expf(-a)) * usum[i]);
       } else {
         float* pr = g.P + ((int64_t)split * g.M + m) * g.N + nb * 128 + ln;
         pr[t0 * 16] = gsum[i];
@@ -418,19 +415,6 @@ __global__ void __launch_bounds__(NQ * 128) __attribute__((amdgpu_waves_per_eu(1
     for (int q = 0; q < HI; ++q)
       out_tile(LO + q, acc[LO + q][0] + xs[xidx(0, q, 0)], acc[LO + q][1] + xs[xidx(0, q, 1)]);
   }
-}
-
-// Gate/up in workgroups of 96 columns: where these still are one round of the 256
-// CUs they keep more of them streaming (24576 columns: 256 against 192; each CU
-// takes in weights and activations at some 45 GB/s and no more).  33 / 64 / 80 /
-// 96 / 128 / 160 rows 31.7 / 34.7 / 37.8 / 41.1 / 44.5 / 50.4 us (k_gemm, this
-// kernel with four quarters or the tiled one) -> 30.2 / 32.2 / 33.5 / 35.6 / 40.8 /
-// 47.3; up to 32 rows both take the same time, at 176 and 192 the tiled kernel is
-// ahead (51 against 55).
-bool narrow_gate_up(int N, int K) { return K == 64 * KS && N % 96 == 0 && N / 96 <= 256; }
-template <int RT>
-void go_narrow(const GemmArgs& g, hipStream_t st) {
-  k_gemm_x2c<RT, 64, EPI_SWIGLU, 3><<<g.N / 96, 384, 0, st>>>(g);
 }
 
 template <int MT>
@@ -508,8 +492,7 @@ bool launch_x2c_64(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   dim3 grid(g.N / 128, splits, 1);
   if (epi == EPI_SWIGLU) {
     if (steps != 64) return false;
-    if (narrow_gate_up(g.N, g.K)) go_narrow<4>(g, st);
-    else k_gemm_x2c<4, 64, EPI_SWIGLU><<<grid, 512, 0, st>>>(g);
+    k_gemm_x2c<4, 64, EPI_SWIGLU><<<grid, 512, 0, st>>>(g);
   } else if (steps == 24) {
     k_gemm_x2c<4, 24, EPI_PARTIAL><<<grid, 512, 0, st>>>(g);
   } else if (steps == 8) {
@@ -548,18 +531,7 @@ bool launch_x2c_80(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   return true;
 }
 
-bool gemm_takes(int M, int N, int K, int epi) {
-  return M <= kTileRows || (epi == EPI_SWIGLU && M <= 160 && narrow_gate_up(N, K));
-}
-
 void launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t st) {
-  if (g.M > 64 && epi == EPI_SWIGLU && narrow_gate_up(g.N, g.K)) {
-    if (g.M <= 80) go_narrow<5>(g, st);
-    else if (g.M <= 96) go_narrow<6>(g, st);
-    else if (g.M <= 128) go_narrow<8>(g, st);
-    else go_narrow<10>(g, st);
-    return;
-  }
   if (g.M > 32 && g.M <= 64 && epi != EPI_ARGMAX && launch_x2c_64(g, epi, splits, st)) return;
   if (g.M > 64 && g.M <= 80 && launch_x2c_80(g, epi, splits, st)) return;
   switch (cdiv_i(g.M, 16)) {
@@ -567,6 +539,6 @@ void launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t st) {
     case 2: launch_mt<2>(g, epi, splits, st); break;
     case 3: launch_mt<3>(g, epi, splits, st); break;
     case 4: launch_mt<4>(g, epi, splits, st); break;
-    default: launch_mt<5>(g, epi, splits, st); break;  // at most kTileRows rows (gemm_takes)
+    default: launch_mt<5>(g, epi, splits, st); break;  // at most kTileRows rows
   }
 }

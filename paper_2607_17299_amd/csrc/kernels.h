@@ -108,11 +108,10 @@ void launch_append_read(const PoolDev& p, int n, const int32_t* seq, const int32
                         const int32_t* tokens, int vocab, int flags, int32_t* out, hipStream_t st);
 void launch_add_ctx(int n, int32_t* ctx, const int32_t* add, hipStream_t st);
 
-// GEMM of at most kTileRows rows, or what else gemm_takes says (gemm.hip)
+// GEMM of at most kTileRows rows (gemm.hip)
 constexpr int kTileRows = 80;
-bool gemm_takes(int M, int N, int K, int epi);
 void launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t st);
-// GEMM over tiles in LDS, for the rest (gemm_tile.hip): the tile
+// GEMM over tiles in LDS, for more than kTileRows rows (gemm_tile.hip): the tile
 // shape, splits and k range a split that suit a shape, with the partial sums
 // within cap_elems; shape -1 when none fits.
 struct TilePlan {

@@ -427,16 +427,15 @@ war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_r
   const bool fuse = swiglu_out != nullptr;
   const int epi = argmax ? EPI_ARGMAX : fuse ? EPI_SWIGLU : EPI_PARTIAL;
   // the paired gate/up layout is only read by the SwiGLU epilogue: one split
-  const bool tiled = !gemm_takes(M, N, K, epi);
   Split sp{1, K};
   TilePlan tp{-1, 1, K};
-  if (tiled) {
+  if (M > kTileRows) {
     tp = plan_gemm_tile(M, N, K, epi, p_cap);
     sp = {tp.splits, tp.kper};
   } else if (epi == EPI_PARTIAL) {
     sp = pick_split(M, N, K, std::min(p_cap, kPartialCap));
   }
-  if ((tiled && tp.shape < 0) || (epi == EPI_PARTIAL && (int64_t)sp.s * M * N > w.p_elems))
+  if ((M > kTileRows && tp.shape < 0) || (epi == EPI_PARTIAL && (int64_t)sp.s * M * N > w.p_elems))
     return fail(WAR_ERR_INVALID_ARG, "internal: split-K partials exceed the workspace");
   g.kper = sp.kper;
   g.out = swiglu_out;
@@ -446,7 +445,7 @@ war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_r
   g.ld_logits = N;
   g.amax_v = w.amax_v;
   g.amax_i = w.amax_i;
-  if (tiled) launch_gemm_tile(g, epi, tp.shape, sp.s, st);
+  if (M > kTileRows) launch_gemm_tile(g, epi, tp.shape, sp.s, st);
   else launch_gemm(g, epi, sp.s, st);
   if (splits_out) *splits_out = sp.s;
   return WAR_OK;

@@ -108,27 +108,3 @@ def test_narrow_matrices_match_oracle(d, heads, ffn, B, k):
         kv = synth.kv_context(cfg, 4, b, 0, 0, ctx[b], DEV).cpu().double().numpy()
         r = verify_request(cfg, W, RequestKV(cfg, [(kv[0], kv[1])]), int(last[b]), drafts[b][:k].tolist())
         assert np.abs(r["logits"] - got[b]).max() <= LOGIT_TOL
-
-
-@pytest.mark.parametrize("rows", [33, 49, 64, 65, 80, 81, 97, 128, 129, 160, 161])
-def test_gate_up_rows_match_small_passes(models, rows):
-    """Gate/up in 96-column workgroups (33-160 rows; row tiles of 64, 80, 96, 128
-    and 160) against steps of at most 32 rows, one request a row."""
-    war = models["war"]
-    pool = war.Pool(CFG, rows * 2, rows, 2)
-    ctx = [1 + (5 * b) % 13 for b in range(rows)]
-    harness.load_contexts(pool, CFG, ctx, list(range(rows)), kv_seed=6)
-    last = np.random.default_rng(rows).integers(0, CFG.vocab, rows)
-
-    def step(lo, hi):
-        n = hi - lo
-        logits = torch.zeros((n, CFG.vocab), device=DEV)
-        seq, c = _t(range(lo, hi)), _t(ctx[lo:hi])
-        war.verify_step(models["many"], pool, seq, c, _t(last[lo:hi]), _t(np.zeros((n, 1))), None, 0, _t([0] * n),
-                        _t([0] * n), logits)
-        war.kv_commit(pool, seq, c, _t([-1] * n))
-        torch.cuda.synchronize()
-        return logits
-
-    ref = torch.cat([step(lo, min(rows, lo + 32)) for lo in range(0, rows, 32)])
-    assert (step(0, rows) - ref).abs().max() <= LOGIT_TOL
