@@ -243,6 +243,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))
             idx = oi;
           }
         }
+        if (g.nan_max) {  // the comparisons drop most NaNs
+          const unsigned long long nan = __ballot(acc[mt][0][i] != acc[mt][0][i] || v1 != v1);
+          if ((nan >> (lg * 16)) & 0xffff) v = __builtin_nanf("");
+        }
         if (ln == 0) {
           sv[w * MT * 16 + r] = v;
           si[w * MT * 16 + r] = idx;
@@ -257,7 +261,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))
       for (int ww = 1; ww < 4; ++ww) {
         const float ov = sv[ww * MT * 16 + r];
         const int oi = si[ww * MT * 16 + r];
-        if (ov > v || (ov == v && oi < idx)) {
+        if (ov > v || (ov == v && oi < idx) || (g.nan_max && ov != ov)) {
           v = ov;
           idx = oi;
         }

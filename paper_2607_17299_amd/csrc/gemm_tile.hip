@@ -261,6 +261,12 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
             idx = oi;
           }
         }
+        if (g.nan_max) {  // the comparisons drop most NaNs
+          bool has = false;
+#pragma unroll
+          for (int n = 0; n < NT; ++n) has |= acc[m][n][i] != acc[m][n][i];
+          if ((__ballot(has) >> (lg * 16)) & 0xffff) v = __builtin_nanf("");
+        }
         if (ln == 0) {
           sv[wn * BM + row - m0] = v;
           si[wn * BM + row - m0] = idx;
@@ -276,7 +282,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
       for (int w = 1; w < WPG; ++w) {
         const float ov = sv[(gi * WPG + w) * BM + r];
         const int oi = si[(gi * WPG + w) * BM + r];
-        if (ov > v || (ov == v && oi < idx)) {
+        if (ov > v || (ov == v && oi < idx) || (g.nan_max && ov != ov)) {
           v = ov;
           idx = oi;
         }

@@ -69,6 +69,7 @@ struct GemmArgs {
   int64_t ld_logits;
   float* amax_v;
   int32_t* amax_i;
+  int nan_max;  // argmax epilogue: a block that holds a NaN gets a NaN best value
 };
 
 enum { EPI_PARTIAL = 0, EPI_ARGMAX = 1, EPI_SWIGLU = 2 };
@@ -135,8 +136,8 @@ struct SampleArgs {
   const float* uniforms;   // [B * kp1][2]: acceptance test, draw
   float temperature;
   int top_k;
-  // nullable: [B * kp1][V / 128], the largest logit of each 128-id block (the
-  // LM head's argmax partials)
+  // nullable: [B * kp1][V / 128], the largest logit of each 128-id block, NaN
+  // where the block holds one (the LM head's argmax partials with nan_max)
   const float* block_max;
   int32_t* row_out;        // [B * kp1][3]: accepted?, token if rejected here, token if last
 };

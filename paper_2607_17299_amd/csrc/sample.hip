@@ -29,7 +29,7 @@
 // then ordered passes (each wave walks its own id segment in coalesced 64-id
 // chunks, with wave scans).  It takes what the blocks cannot narrow down: more
 // kept ids than blocks, rows with more candidates than fit LDS (many equal
-// logits), NaN block maxima.
+// logits), rows with a NaN (a block that holds one has a NaN maximum).
 #include "kernels.h"
 
 namespace {
@@ -519,8 +519,9 @@ __global__ void __launch_bounds__(kST) k_sample_rows(SampleArgs s) {
 // LM head's epilogue leaves, for logits that come from elsewhere.
 __global__ void __launch_bounds__(64) k_block_max(const float* z, int V, float* block_max) {
   const int64_t at = (int64_t)blockIdx.y * V + (int64_t)blockIdx.x * kBlk + threadIdx.x;
-  const float m = wave_max(fmaxf(z[at], z[at + 64]));
-  if (threadIdx.x == 0) block_max[(int64_t)blockIdx.y * (V / kBlk) + blockIdx.x] = m;
+  const float a = z[at], b = z[at + 64], m = wave_max(fmaxf(a, b));
+  const bool nan = __any(a != a || b != b);
+  if (threadIdx.x == 0) block_max[(int64_t)blockIdx.y * (V / kBlk) + blockIdx.x] = nan ? __builtin_nanf("") : m;
 }
 
 __global__ void k_sample_accept(SampleArgs s, int32_t* accept_lens, int32_t* next_tokens) {

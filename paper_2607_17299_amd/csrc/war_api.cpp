@@ -415,7 +415,7 @@ int64_t partials_needed(const ModelDims& md, int R) {
 // p_cap bounds the partial elements (partials_needed of the pass).
 war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_rows, const bf16_t* Wp,
                 int M, int N, int K, int64_t p_cap, int* splits_out, hipStream_t st, bool argmax = false,
-                float* logits = nullptr, bf16_t* swiglu_out = nullptr) {
+                float* logits = nullptr, bf16_t* swiglu_out = nullptr, bool nan_max = false) {
   GemmArgs g{};
   g.A = A;
   g.lda = lda;
@@ -445,6 +445,7 @@ war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_r
   g.ld_logits = N;
   g.amax_v = w.amax_v;
   g.amax_i = w.amax_i;
+  g.nan_max = nan_max;
   if (M > kTileRows) launch_gemm_tile(g, epi, tp.shape, sp.s, st);
   else launch_gemm(g, epi, sp.s, st);
   if (splits_out) *splits_out = sp.s;
@@ -1064,7 +1065,8 @@ war_status verify_impl(war_model* m, war_kv_pool* p, int32_t B, const int32_t* s
     HIPCHK(m->row_out.ensure((size_t)R * 3 * 4));
     {
       Timed t(m->prof, st, "gemm_lm_head");
-      WARCHK(gemm(w, w.u, m->md.d, nullptr, m->w_lm, R, m->md.V, m->md.d, 0, &sdummy, st, true, lg));
+      WARCHK(gemm(w, w.u, m->md.d, nullptr, m->w_lm, R, m->md.V, m->md.d, 0, &sdummy, st, true, lg, nullptr,
+                  true));
     }
     SampleArgs sa{};
     sa.logits = lg;

@@ -104,3 +104,79 @@ def test_sampling_block_bound_edges(V, top_k, alter):
     below 1e-5, fp32 sums against float64, are reported)."""
     exact, report, _ = _case(V, 4, 2, 1.0, top_k, 2.0, seed=V + top_k, alter=alter)
     assert exact + len(report) == 4 and len(report) <= 1, report
+
+
+def _nan_rule(z, d, u, v, top_k):
+    """(accepted?, token if rejected here, token if last) of a row that may hold
+    NaNs: a positive one sorts above every number and is kept, a negative one
+    below.  A kept NaN makes the total weight NaN: no draft is accepted and no
+    cumulative weight exceeds the target, which leaves the highest kept id (other
+    than a rejected draft) of nonzero weight."""
+    bits = (z + np.float32(0)).view(np.uint32)
+    key = np.where(bits >> 31, ~bits, bits | np.uint32(0x80000000))
+    kept = np.sort(np.lexsort((np.arange(z.size), -key.astype(np.int64)))[:top_k])
+    if np.isnan(z[kept]).any():
+        live = kept[~np.isnan(z[kept])]
+        return False, int(live[live != d].max()), int(live.max())
+    clean = np.where(np.isnan(z), -np.inf, z).astype(np.float64)
+    r = verify_sampled(np.stack([clean, clean]), [int(d)] if d >= 0 else [], [u, u], [v, v], 1.0, top_k)
+    end = verify_sampled(clean[None], [], [u], [v], 1.0, top_k)["next"]
+    return bool(r["accept"]) and d >= 0, r["next"], end
+
+
+def _decide(rows, drafts, u, top_k):
+    for i in range(len(rows)):
+        d = drafts[i] if i < len(drafts) else -1
+        ok, rej, end = _nan_rule(rows[i], d, u[i, 0], u[i, 1], top_k)
+        if i < len(drafts) and ok:
+            continue
+        return i, rej if i < len(drafts) else end
+
+
+@pytest.mark.parametrize("where", ["best block", "worst block", "several"])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_sampling_rows_with_nan(where, sign):
+    """A NaN logit, in a block that the block maxima select, in one that they do
+    not, in each lane of both halves of a block: the decisions of the row walk."""
+    from paper_2607_17299_amd import war
+    V, B, k, top_k = 8192, 64, 1, 20
+    rng = np.random.default_rng(11)
+    z = (rng.standard_normal((B * (k + 1), V)) * 2).astype(np.float32)
+    nan = np.array([0x7fc00000 if sign > 0 else 0xffc00000], np.uint32).view(np.float32)[0]
+    for r in range(z.shape[0]):
+        best = z[r].reshape(-1, 128).max(1).argsort()
+        blk = best[-1] if where == "best block" else best[0]
+        z[r, blk * 128 + r] = nan                       # B * (k + 1) = 128 rows: every position once
+        if where == "several":
+            z[r, rng.choice(V, 3, replace=False)] = nan
+    drafts = z[::2].argsort(1)[:, -2:-1].astype(np.int32)
+    u = rng.random((B * (k + 1), 2)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    acc, nxt = (torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(2))
+    war.debug_sample(dev(z), dev(np.full(B, k + 1, np.int32)), dev(drafts), k, dev(u), 1.0, top_k, acc, nxt)
+    got = list(zip(acc.cpu().tolist(), nxt.cpu().tolist()))
+    want = [_decide(z[2 * b: 2 * b + 2], drafts[b].tolist(), u[2 * b: 2 * b + 2], top_k) for b in range(B)]
+    assert got == want
+
+
+@pytest.mark.parametrize("B", [4, 40])               # 12 and 120 rows: both LM-head kernels
+@pytest.mark.parametrize("col", [0, 17, 63, 100, 127])
+def test_sampled_step_with_a_nan_column(B, col):
+    """A NaN weight in one LM-head row: every row's logits hold one NaN."""
+    from paper_2607_17299_amd import harness, synth, war
+    cfg, k, top_k = synth.reduced(synth.TINY, 1), 2, 20
+    w = {n: t.cuda() for n, t in synth.model_weights(cfg, seed=0, norm_std=0.1).items()}
+    w["w_lm"][5 * 128 + col, 3] = float("nan")
+    model, pool = war.Model(cfg, w, max_rows=128), war.Pool(cfg, 2 * B, B, 2)
+    t = lambda a: torch.as_tensor(np.asarray(a), dtype=torch.int32).cuda()
+    ctx = [1 + b % 20 for b in range(B)]
+    harness.load_contexts(pool, cfg, ctx, list(range(B)), kv_seed=3)
+    rng = np.random.default_rng(B)
+    drafts, u = rng.integers(0, cfg.vocab, (B, k)), rng.random((B * (k + 1), 2)).astype(np.float32)
+    acc, nxt, logits = t([0] * B), t([0] * B), torch.zeros((B * (k + 1), cfg.vocab), device="cuda")
+    war.verify_step_sampled(model, pool, t(range(B)), t(ctx), t(rng.integers(0, cfg.vocab, B)), t(drafts), None, k,
+                            torch.from_numpy(u).cuda(), 1.0, top_k, acc, nxt, logits)
+    z = logits.cpu().numpy().reshape(B, k + 1, -1)
+    assert (np.isnan(z).sum(-1) == 1).all()
+    want = [_decide(z[b], drafts[b].tolist(), u.reshape(B, k + 1, 2)[b], top_k) for b in range(B)]
+    assert list(zip(acc.cpu().tolist(), nxt.cpu().tolist())) == want
