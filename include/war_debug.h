@@ -40,6 +40,13 @@ war_status war_debug_sample(const float* logits, int32_t V, int32_t B, int32_t k
                             const int32_t* drafts, const float* uniforms, float temperature, int32_t top_k,
                             int32_t* accept_lens, int32_t* next_tokens, void* stream);
 
+/* The kernel a product of M rows with an [N][K] matrix takes (host only, no
+ * device is touched).  epi: 0 partial sums, 1 the LM head's argmax, 2 SwiGLU;
+ * cap_elems bounds the partial sums.  HOST out: the tile shape (-1: the few-row
+ * kernels), the splits of K (0: none fits) and the k range of a split. */
+war_status war_debug_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epi, int64_t cap_elems, int32_t* shape,
+                               int32_t* splits, int32_t* kper);
+
 /* How many times the pool's verify steps read the exact free page count from
  * the device (each such read waits for the stream) because the host's lower
  * bound did not cover the step's worst-case reservation (HOST out). */

@@ -5,7 +5,8 @@
 // against N x K weights of 16-310 MB, so the kernel is bound by streaming W
 // from HBM: every weight byte is read exactly once.  (More rows run in
 // gemm_tile.hip: at 96 rows qkv 14.9 -> 12.5 us, o 11.3 -> 10.2, down 25.2 ->
-// 22.8, gate/up 40.7 -> 41; at 80 rows gate/up and qkv are slower there.)
+// 22.8, gate/up 40.7 -> 41; at 80 rows gate/up and qkv are slower there.  A large
+// LM head stays here up to 96 rows.)
 //
 // Weights are repacked once, when the model is created, into MFMA fragment
 // order: for n-tile nt (16 output rows), k-step s (64 inputs) and half j, the
@@ -422,14 +423,20 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))
 }
 
 template <int MT>
+void launch_argmax(const GemmArgs& g, hipStream_t st) {
+  const int steps = g.kper / KS, grid = g.N / 128;
+  if (steps == 64) k_gemm<MT, 64, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
+  else if (steps == 16) k_gemm<MT, 16, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
+  else k_gemm<MT, 0, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
+}
+
+template <int MT>
 void launch_mt(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   dim3 grid(g.N / 128, splits, 1);
   const int steps = g.kper / KS;
   const bool exact = (int64_t)g.kper * splits == g.K;
   if (epi == EPI_ARGMAX) {
-    if (steps == 64) k_gemm<MT, 64, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
-    else if (steps == 16) k_gemm<MT, 16, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
-    else k_gemm<MT, 0, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
+    launch_argmax<MT>(g, st);
   } else if (epi == EPI_SWIGLU) {
     if (steps == 64) k_gemm<MT, 64, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
     else if (steps == 16) k_gemm<MT, 16, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
@@ -543,6 +550,7 @@ void launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t st) {
     case 2: launch_mt<2>(g, epi, splits, st); break;
     case 3: launch_mt<3>(g, epi, splits, st); break;
     case 4: launch_mt<4>(g, epi, splits, st); break;
-    default: launch_mt<5>(g, epi, splits, st); break;  // at most kTileRows rows
+    case 5: launch_mt<5>(g, epi, splits, st); break;
+    default: launch_argmax<6>(g, st); break;  // a large LM head at 81-96 rows
   }
 }

@@ -109,12 +109,17 @@ void launch_append_read(const PoolDev& p, int n, const int32_t* seq, const int32
                         const int32_t* tokens, int vocab, int flags, int32_t* out, hipStream_t st);
 void launch_add_ctx(int n, int32_t* ctx, const int32_t* add, hipStream_t st);
 
-// GEMM of at most kTileRows rows (gemm.hip)
-constexpr int kTileRows = 80;
+// GEMM of few rows (gemm.hip): at most 80, or 96 where gemm_tiled says so
 void launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t st);
-// GEMM over tiles in LDS, for more than kTileRows rows (gemm_tile.hip): the tile
-// shape, splits and k range a split that suit a shape, with the partial sums
-// within cap_elems; shape -1 when none fits.
+// Whether a product runs in gemm_tile.hip.  More than 80 rows do, but an LM head of
+// more than 256 128-id blocks from 97 on: at 81-96 rows its tiles make a nearly
+// empty second round over the CUs where the streaming kernel, several workgroups a
+// CU, stays at the weights' rate.  96 rows of a 4096-wide decoder: 32,768 ids 55.6 us
+// streaming, 52.5 tiled; 36,864 ids 83 and 91, 65,536 ids 96 and 137, 151,936 ids
+// 216 and 289 (at 112 rows 300 and 283).
+inline bool gemm_tiled(int M, int N, int epi) { return M > (epi == EPI_ARGMAX && N > 256 * 128 ? 96 : 80); }
+// GEMM over tiles in LDS (gemm_tile.hip): the tile shape, splits and k range a split
+// that suit a shape, with the partial sums within cap_elems; shape -1 when none fits.
 struct TilePlan {
   int shape, splits, kper;
 };

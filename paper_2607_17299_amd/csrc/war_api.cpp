@@ -411,6 +411,19 @@ int64_t partials_needed(const ModelDims& md, int R) {
   return n;
 }
 
+// The kernel of a projection: a tile shape of gemm_tile.hip (-1: gemm.hip), the
+// splits and k range a split.  splits 0 when the partials do not fit cap_elems.
+TilePlan plan_gemm(int M, int N, int K, int epi, int64_t cap_elems) {
+  if (gemm_tiled(M, N, epi)) {
+    const TilePlan tp = plan_gemm_tile(M, N, K, epi, cap_elems);
+    return tp.shape < 0 ? TilePlan{-1, 0, K} : tp;
+  }
+  // the paired gate/up layout is only read by the SwiGLU epilogue: one split
+  if (epi != EPI_PARTIAL) return {-1, 1, K};
+  const Split sp = pick_split(M, N, K, std::min(cap_elems, kPartialCap));
+  return {-1, sp.s, sp.kper};
+}
+
 // One projection: P[split][M][N] = A x W^T (or the LM-head argmax epilogue).
 // p_cap bounds the partial elements (partials_needed of the pass).
 war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_rows, const bf16_t* Wp,
@@ -424,20 +437,11 @@ war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_r
   g.M = M;
   g.N = N;
   g.K = K;
-  const bool fuse = swiglu_out != nullptr;
-  const int epi = argmax ? EPI_ARGMAX : fuse ? EPI_SWIGLU : EPI_PARTIAL;
-  // the paired gate/up layout is only read by the SwiGLU epilogue: one split
-  Split sp{1, K};
-  TilePlan tp{-1, 1, K};
-  if (M > kTileRows) {
-    tp = plan_gemm_tile(M, N, K, epi, p_cap);
-    sp = {tp.splits, tp.kper};
-  } else if (epi == EPI_PARTIAL) {
-    sp = pick_split(M, N, K, std::min(p_cap, kPartialCap));
-  }
-  if ((M > kTileRows && tp.shape < 0) || (epi == EPI_PARTIAL && (int64_t)sp.s * M * N > w.p_elems))
+  const int epi = argmax ? EPI_ARGMAX : swiglu_out ? EPI_SWIGLU : EPI_PARTIAL;
+  const TilePlan tp = plan_gemm(M, N, K, epi, p_cap);
+  if (tp.splits == 0 || (epi == EPI_PARTIAL && (int64_t)tp.splits * M * N > w.p_elems))
     return fail(WAR_ERR_INVALID_ARG, "internal: split-K partials exceed the workspace");
-  g.kper = sp.kper;
+  g.kper = tp.kper;
   g.out = swiglu_out;
   g.ld_out = N / 2;
   g.P = w.P;
@@ -446,9 +450,9 @@ war_status gemm(const Workspace& w, const bf16_t* A, int lda, const int32_t* a_r
   g.amax_v = w.amax_v;
   g.amax_i = w.amax_i;
   g.nan_max = nan_max;
-  if (M > kTileRows) launch_gemm_tile(g, epi, tp.shape, sp.s, st);
-  else launch_gemm(g, epi, sp.s, st);
-  if (splits_out) *splits_out = sp.s;
+  if (tp.shape >= 0) launch_gemm_tile(g, epi, tp.shape, tp.splits, st);
+  else launch_gemm(g, epi, tp.splits, st);
+  if (splits_out) *splits_out = tp.splits;
   return WAR_OK;
 }
 
@@ -1433,6 +1437,18 @@ war_status war_debug_sample(const float* logits, int32_t V, int32_t B, int32_t k
   rows.release();
   bmax.release();
   HIPCHK(e);
+  return WAR_OK;
+}
+
+war_status war_debug_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epi, int64_t cap_elems, int32_t* shape,
+                               int32_t* splits, int32_t* kper) {
+  CHECK(shape && splits && kper, "null argument");
+  CHECK(M >= 1 && N >= 128 && N % 128 == 0 && K >= 64 && K % 64 == 0, "bad sizes");
+  CHECK(epi == EPI_PARTIAL || epi == EPI_ARGMAX || epi == EPI_SWIGLU, "bad epilogue");
+  const TilePlan tp = plan_gemm(M, N, K, epi, cap_elems);
+  *shape = tp.shape;
+  *splits = tp.splits;
+  *kper = tp.kper;
   return WAR_OK;
 }
 

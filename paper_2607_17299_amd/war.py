@@ -29,7 +29,7 @@ EXPORTS = ["war_weight_count", "war_model_create", "war_model_destroy", "war_kv_
            "war_verify_step_noalloc",
            "war_kv_commit", "war_pool_state",
            "war_last_error", "war_debug_mfma16", "war_debug_workspace", "war_debug_sample",
-           "war_debug_pool_waits", "war_profile", "war_profile_read"]
+           "war_debug_gemm_plan", "war_debug_pool_waits", "war_profile", "war_profile_read"]
 
 
 class WarError(RuntimeError):
@@ -72,6 +72,7 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
         "war_debug_sample": (i32, [vp, i32, i32, i32, vp, vp, vp, C.c_float, i32, vp, vp, vp]),
         "war_debug_mfma16": (i32, [vp, vp, vp, vp]),
         "war_debug_workspace": (i32, [vp, C.c_char_p, C.POINTER(vp), C.POINTER(C.c_int64)]),
+        "war_debug_gemm_plan": (i32, [i32, i32, i32, i32, C.c_int64, pi32, pi32, pi32]),
         "war_debug_pool_waits": (i32, [vp, C.POINTER(C.c_int64)]),
         "war_profile": (i32, [vp, i32]),
         "war_profile_read": (i32, [vp, C.c_char_p, i32]),
@@ -315,6 +316,13 @@ def debug_sample(logits: torch.Tensor, ntok: torch.Tensor, drafts: torch.Tensor,
     _check(lib().war_debug_sample(_ptr(logits), V, B, k_max, _ptr(ntok), _ptr(drafts), _ptr(uniforms),
                                   float(temperature), int(top_k), _ptr(accept_lens), _ptr(next_tokens),
                                   _stream(stream)))
+
+
+def debug_gemm_plan(M: int, N: int, K: int, epi: int, cap_elems: int = 64 << 20) -> tuple:
+    """(tile shape or -1, splits, k range of a split) of a product (war_debug.h)."""
+    out = [C.c_int32() for _ in range(3)]
+    _check(lib().war_debug_gemm_plan(M, N, K, epi, cap_elems, *[C.byref(x) for x in out]))
+    return tuple(x.value for x in out)
 
 
 def debug_workspace(model: Model, name: str, dtype: torch.dtype, shape) -> torch.Tensor:

@@ -108,3 +108,31 @@ def test_narrow_matrices_match_oracle(d, heads, ffn, B, k):
         kv = synth.kv_context(cfg, 4, b, 0, 0, ctx[b], DEV).cpu().double().numpy()
         r = verify_request(cfg, W, RequestKV(cfg, [(kv[0], kv[1])]), int(last[b]), drafts[b][:k].tolist())
         assert np.abs(r["logits"] - got[b]).max() <= LOGIT_TOL
+
+
+@pytest.mark.parametrize("rows", [81, 96, 97])
+@pytest.mark.parametrize("d", [256, 1024, 4096])      # loops of 4 k-steps, and 16 and 64 unrolled
+def test_large_lm_head_rows_match_small_steps(rows, d):
+    """A head of 257 128-id blocks at the row counts where its kernel changes,
+    against the same requests in steps of 27: the rows' logits and argmax."""
+    from paper_2607_17299_amd import war
+    cfg = synth.ModelConfig(n_layers=1, d_model=d, n_q_heads=2, n_kv_heads=2, head_dim=128, ffn_dim=256,
+                            vocab=257 * 128)
+    g = torch.Generator(device=DEV).manual_seed(d)
+    w = {n: torch.empty(s, dtype=torch.bfloat16, device=DEV).normal_(0, 0.02 if len(s) > 1 else 0.5, generator=g)
+         for n, s in synth.weight_shapes(cfg)}
+    model, pool = war.Model(cfg, w, max_rows=128), war.Pool(cfg, rows, rows, 2)
+    last = np.random.default_rng(d).integers(0, cfg.vocab, rows)
+
+    def step(lo, hi):
+        n = hi - lo
+        acc, nxt, logits = _t([0] * n), _t([0] * n), torch.zeros((n, cfg.vocab), device=DEV)
+        war.verify_step(model, pool, _t(range(lo, hi)), _t([0] * n), _t(last[lo:hi]), None, None, 0, acc, nxt, logits)
+        war.kv_commit(pool, _t(range(lo, hi)), _t([0] * n), _t([-1] * n))
+        torch.cuda.synchronize()
+        return logits, nxt
+
+    got = step(0, rows)
+    ref = torch.cat([step(lo, min(rows, lo + 27))[0] for lo in range(0, rows, 27)])
+    assert (got[0] - ref).abs().max() <= LOGIT_TOL
+    assert torch.equal(got[1].long(), (got[0] == got[0].amax(-1, keepdim=True)).int().argmax(-1))
