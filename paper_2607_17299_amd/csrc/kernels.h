@@ -111,6 +111,12 @@ void launch_add_ctx(int n, int32_t* ctx, const int32_t* add, hipStream_t st);
 
 // GEMM of few rows (gemm.hip): at most 80, or 96 where gemm_tiled says so
 void launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t st);
+// Whether splits of `steps` k-steps have a fully unrolled kernel there at M rows.
+inline bool gemm_unrolled(int M, int steps) {
+  for (int s : {1, 2, 4, 8, 12, 16, 24, 32, 48})
+    if (steps == s) return true;
+  return steps == 64 && M > 32 && M <= 64;
+}
 // Whether a product runs in gemm_tile.hip.  More than 80 rows do, but an LM head of
 // more than 256 128-id blocks from 97 on: at 81-96 rows its tiles make a nearly
 // empty second round over the CUs where the streaming kernel, several workgroups a

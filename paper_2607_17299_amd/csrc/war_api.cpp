@@ -363,22 +363,36 @@ struct Timed {
   }
 };
 
-// Split-K of the skinny kernels: the most splits that divide K exactly (the fully
-// unrolled kernels need that) with no more than one workgroup a CU.  Fewer leave
-// CUs idle, more make a second round: the 4096 x 12288 down projection at 80 rows
-// takes 28.7 us in 128 workgroups, 22.4 in 192, 18.9 in 256 and 26.3 in 288; a
+// Split-K of the few-row kernels: the most splits that divide K exactly with no
+// more than one workgroup a CU, if their k-step count has an unrolled kernel.  Fewer
+// leave CUs idle, more make a second round: the 4096 x 12288 down projection at 80
+// rows takes 28.7 us in 128 workgroups, 22.4 in 192, 18.9 in 256 and 26.3 in 288; a
 // 1024 x 1024 matrix at 66 rows 9.6 us in 8 workgroups, 5.1 in 64, 4.8 in 128.
+// A count that leaves the runtime loop (4096 x 14336 in 8 splits of 28 steps) is
+// weighed against bound_split's (7 of 32): 0.6 us a k-step of the busiest CU, 0.9 of
+// that where workgroups share it, 3 us for the runtime loop's exposed loads, and 0.4 us
+// and 0.1 us a MB for each split's sums at their consumer.  Over 65 matrices at 1-80
+// rows the choice is within 3% of the better of the two; the larger count taken
+// always cost up to 20% there: 72 rows with the consumer, 4096 x 14336 36.8 us -> 33.3,
+// 5120 x 17408 58.9 -> 52.6, 3584 x 3584 21.6 -> 19.8, 10240 x 8192 57.4 -> 49.6.
 // Matrices that cannot be cut into 128 workgroups (and partial sums beyond
 // cap_elems) take what bound_split says.
 Split bound_split(int M, int N, int K, int64_t cap_elems);
 Split pick_split(int M, int N, int K, int64_t cap_elems) {
+  const Split few = bound_split(M, N, K, cap_elems);
   const int groups = N / 128, steps = K / 64;
-  if (groups <= 256 && groups * steps >= 128) {
-    int s = std::min(256 / groups, steps);
-    while (steps % s) --s;
-    if (groups * s >= 128 && (int64_t)s * M * N <= cap_elems) return {s, K / s};
-  }
-  return bound_split(M, N, K, cap_elems);
+  if (groups > 256 || groups * steps < 128) return few;
+  int s = std::min(256 / groups, steps);
+  while (steps % s) --s;
+  if (groups * s < 128 || (int64_t)s * M * N > cap_elems) return few;
+  const Split most{s, K / s};
+  auto unrolled = [&](const Split& x) { return (int64_t)x.s * x.kper == K && gemm_unrolled(M, x.kper / 64); };
+  auto cost = [&](const Split& x) {
+    const int wgs = groups * x.s;
+    return cdiv_i(wgs, 256) * (x.kper / 64) * (wgs > 256 ? 0.54 : 0.6) + (unrolled(x) ? 0 : 3) +
+           x.s * (0.4 + 0.1 * 4e-6 * M * N);
+  };
+  return unrolled(most) || cost(most) <= cost(few) ? most : few;
 }
 
 // The count the workspace of a step is sized by (the partial sums of all its

@@ -21,3 +21,31 @@ def test_large_lm_heads_stream_up_to_96_rows(M, ids, tiled):
     for K in (1024, 4096, 5120):
         shape, splits, kper = _plan(M, ids, K, ARGMAX)
         assert (shape >= 0) == tiled and (splits, kper) == (1, K)
+
+
+# (N, K, rows, splits): counts of an unrolled kernel, or the runtime loop where that
+# is still the faster (11008, 28672, 15360: the other count has far more workgroups
+# than CUs, or fewer and a longer loop)
+@pytest.mark.parametrize("N,K,rows,splits", [
+    (4096, 12288, (1, 32, 64, 80), 8), (6144, 4096, (1, 48, 80), 4), (4096, 4096, (1, 48, 80), 8),
+    (1024, 1024, (1, 48, 80), 16), (1024, 4096, (1, 48, 80), 32), (1536, 1024, (1, 80), 16),
+    (4096, 14336, (1, 16, 48, 72), 7), (3584, 3584, (1, 16, 48, 72), 7), (2048, 6144, (1, 48, 80), 12),
+    (2560, 9728, (1, 48, 80), 19), (5120, 17408, (1, 16, 48, 72), 8), (6144, 16384, (16, 72), 8),
+    (6144, 16384, (48,), 4), (10240, 8192, (16, 72), 4), (10240, 8192, (48,), 2), (20480, 4096, (16, 72), 2),
+    (4096, 11008, (16, 48, 72), 4), (8192, 28672, (1, 16, 48, 72), 4), (4096, 15360, (1, 48, 72), 8),
+    (7168, 18432, (1, 48, 72), 4)])
+def test_split_counts(N, K, rows, splits):
+    for M in rows:
+        shape, s, kper = _plan(M, N, K, PARTIAL)
+        assert (shape, s, kper) == (-1, splits, K // splits), M
+
+
+@pytest.mark.parametrize("d", [896, 1024, 2048, 2560, 3072, 3584, 4096, 5120, 6144, 8192])
+def test_splits_cover_k_within_the_cap(d):
+    for N, K in [(d, d), (d, 3 * d), (d, 128 * 37), (3 * d // 128 * 128, d)]:
+        for M in (1, 17, 33, 64, 65, 80, 81, 200, 2048):
+            for cap in (64 << 20, 64 * M * N, M * N):
+                shape, s, kper = _plan(M, N, K, PARTIAL, cap)
+                if s == 0:
+                    continue
+                assert kper % 64 == 0 and (s - 1) * kper < K <= s * kper and s * M * N <= cap
