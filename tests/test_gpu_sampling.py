@@ -180,3 +180,10 @@ def test_sampled_step_with_a_nan_column(B, col):
     assert (np.isnan(z).sum(-1) == 1).all()
     want = [_decide(z[b], drafts[b].tolist(), u.reshape(B, k + 1, 2)[b], top_k) for b in range(B)]
     assert list(zip(acc.cpu().tolist(), nxt.cpu().tolist())) == want
+
+
+@pytest.mark.parametrize("V,top_k", [(31 * 128, 31), (31 * 128, 1), (32 * 128, 32), (32 * 128, 1), (33 * 128, 33)])
+def test_sampling_fewest_blocks(V, top_k):
+    """Around 32 blocks, from which on the block maxima narrow a row."""
+    exact, report, _ = _case(V, 6, 3, 1.0, top_k, 2.0, seed=V + top_k)
+    assert exact + len(report) == 6 and len(report) <= 1, report
