@@ -980,7 +980,7 @@ war_status verify_impl(war_model* m, war_kv_pool* p, int32_t B, const int32_t* s
   while (cdiv_i(p->dev.max_pages * P, chunk) > kMaxItemsPerSeq) chunk *= 2;
   int64_t max_items = (int64_t)B * cdiv_i(p->dev.max_pages * P, chunk);
   // a step with few keys takes shorter chunks, up to this many items
-  int items_fill = std::min<int64_t>(std::min(kMaxItemsPerSeq, cdiv_i(kAttnFill, m->md.nkv)),
+  int items_fill = std::min<int64_t>(std::min(kMaxItemsPerSeq, std::max(1, kAttnFill / m->md.nkv)),
                                      (int64_t)B * cdiv_i(p->dev.max_pages * P, 128));
   Workspace wsv;
   if (fixed) {

@@ -118,3 +118,33 @@ def test_shared_pages_of_forked_siblings(models, pages):
     own = {0: 3, 1: -1, 2: -1, 3: 0}
     assert items.tolist() == [[b, 0, c, own[b] if c < shared else 0] for b in range(4) for c in range(n[b])]
     assert sorted(order.tolist()) == [i for i, it in enumerate(items.tolist()) if it[3] >= 0]
+
+
+@pytest.mark.parametrize("heads,kv", [(6, 3), (12, 6), (10, 5), (24, 24)])
+def test_shortened_chunks_fit_the_grid(heads, kv):
+    """Chunks are shortened while the units (items times kv-heads) are no more than
+    the grid's 512 workgroups, also where the kv-heads do not divide 512."""
+    from paper_2607_17299_amd import war
+    cfg = synth.ModelConfig(n_layers=1, d_model=128 * heads // 2, n_q_heads=heads, n_kv_heads=kv, head_dim=64,
+                            ffn_dim=256, vocab=1024)
+    w = {n: t.to(DEV) for n, t in synth.model_weights(cfg, seed=2, norm_std=0.1).items()}
+    model = war.Model(cfg, w, max_rows=64)
+    fill = 512 // kv
+    shortened = 0
+    for B in (1, 3):
+        pool = war.Pool(cfg, B * 1700, B, 1700)
+        pool.kv.zero_()
+        pool.alloc(list(range(B)), [26000] * B)
+        for items in (fill - 1, fill, fill + 1, 2 * fill + 1):
+            for chunk in (128, 256, 512):
+                n = min(items // B * chunk, 26000) - 1
+                lens = [n] + [n - 7] * (B - 1)
+                if n < 1024:
+                    continue
+                got, _, n_units, keys = _plan(war, model, pool, lens, 0)
+                assert n_units == len(got) and keys in (128, 256, 512, 1024)
+                if keys < 1024:
+                    shortened += 1
+                    assert n_units * kv <= 512, (lens, keys)
+        pool.close()
+    assert shortened >= 4
