@@ -134,6 +134,11 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
   __shared__ int s_hash[kHash];
   // chunk lengths 2, 1, 1/2, 1/4 and 1/8 of a.chunk, at least 128
   constexpr int kChunks = 5, kMinShift = 7;
+  // Partials of one request that are still worth a shorter chunk: the merge of more
+  // (two items and more a lane) takes longer than the attention gains.  1-4 kv-heads,
+  // 8000-120000 tokens, attention and merge against twice the chunk: 39 partials 0.90,
+  // 62 1.05, 125 1.10, 250 1.26.
+  constexpr int kMergeMax = 64;
   auto chunks_of = [](int n, int shift) { return (n + (1 << shift) - 1) >> shift; };
   __shared__ int s_cnt[kChunks];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, nt = blockDim.x, nw = nt >> 6;
@@ -216,15 +221,18 @@ __global__ void __launch_bounds__(kBT) k_verify_setup(PoolDev p, VerifySetupArgs
   // and no sequences share pages (siblings that read a shared chunk at the same
   // time find it in L2 more often when the chunks are short).  A step too small
   // for the grid takes shorter chunks, down to one 32-key block a wave, while its
-  // units are no more than fill the grid; where every request fits one chunk
-  // nothing is cut (and nothing has to be merged).
+  // units are no more than fill the grid and no request's partials more than
+  // kMergeMax; where every request fits one chunk nothing is cut (and
+  // nothing has to be merged).
   if (t < kChunks) s_cnt[t] = 0;
   __syncthreads();
   const int len = (t < a.B && !fail) ? ctx + dl + 1 : 0;
   int csh = 31 - __clz(a.chunk);  // log2 of the chunk (a power of two)
   if (w * 64 < a.B)
     for (int c = 0; c < kChunks; ++c) {
-      const int n = wave_scan(chunks_of(len, max(csh + 1 - c, kMinShift)));
+      int n = chunks_of(len, max(csh + 1 - c, kMinShift));
+      if (c > 1 && n > kMergeMax) n = 1 << 20;  // more than the grid takes
+      n = wave_scan(n);
       if (lane == 63) atomicAdd(&s_cnt[c], n);
     }
   __syncthreads();

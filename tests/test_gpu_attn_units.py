@@ -148,3 +148,19 @@ def test_shortened_chunks_fit_the_grid(heads, kv):
                     assert n_units * kv <= 512, (lens, keys)
         pool.close()
     assert shortened >= 4
+
+
+@pytest.mark.parametrize("lens,keys", [
+    ([8191], 128), ([8192], 256), ([16000], 256), ([16384], 512), ([32767], 512), ([32768], 1024), ([60000], 1024),
+    ([16000, 3], 256), ([20000, 19000, 5], 512), ([3, 40000], 1024), ([2000] * 4, 128)])
+def test_shortened_chunks_leave_at_most_64_partials(lens, keys):
+    """One kv-head: 512 items fill the grid, but a request is cut into at most 64."""
+    from paper_2607_17299_amd import war
+    cfg = synth.ModelConfig(n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=256, vocab=1024)
+    w = {n: t.to(DEV) for n, t in synth.model_weights(cfg, seed=2, norm_std=0.1).items()}
+    model, B = war.Model(cfg, w, max_rows=64), len(lens)
+    pool = war.Pool(cfg, sum(n // 16 + 2 for n in lens), B, max(lens) // 16 + 2)
+    pool.kv.zero_()
+    pool.alloc(list(range(B)), lens)
+    items, _, _, got = _plan(war, model, pool, lens, 0)
+    assert got == keys and len(items) == sum(-(-(n + 1) // keys) for n in lens)
