@@ -26,9 +26,10 @@ war_status war_debug_mfma16(const void* A, const void* B, float* C, void* stream
  * partials; "rows", "reqs", "items" step metadata; "order" the attention work
  * order and "n_items" its counts ([0] item slots, [1] units in the work
  * order, [3] keys per attention item, which a verify step's setup chooses:
- * the base length or twice it); "tree" the last tree step's node slots and node masks
- * (int32 [2][max_rows]).  The pointer stays valid until the next call on the
- * model. */
+ * twice the base length down to an eighth of it); "tree" the last tree step's
+ * node slots and node masks (int32 [2][max_rows]); "stage" the device copy of a
+ * prefill chunk's host-built metadata (as large as it has grown).  The pointer
+ * stays valid until the next call on the model. */
 war_status war_debug_workspace(war_model* m, const char* name, void** ptr, int64_t* bytes);
 
 /* The sampled-verification decision kernels alone (those war_verify_step_sampled

@@ -88,6 +88,7 @@ struct Profiler {
 };
 constexpr int kPrefillChunk = 4096;  // keys per attention item when prefilling (chunk-major: L2 serves the row blocks)
 constexpr int kPrefillRows = 128;    // attention rows per prefill row block (k_attn_rows)
+constexpr size_t kStageInts = 16384;  // least size of a prefill chunk's metadata block (64 KiB)
 constexpr int kMaxItemsPerSeq = 512;  // attention chunks one combine merges
 constexpr int kAttnGrid = 512;        // persistent attention grid: 2 workgroups per CU
 // Units that a step too small for the grid is cut into.  One request at 8192
@@ -1307,7 +1308,10 @@ war_status war_prefill_append(war_model* m, war_kv_pool* p, int32_t n, const int
     if (!sg.used) HIPCHK(hipEventCreateWithFlags(&sg.used, hipEventDisableTiming));
     HIPCHK(hipEventSynchronize(sg.used));
     const size_t ints = 4 + udesc.size() * 4 + (size_t)3 * R + 4 * nr + 4 * nseg + nl + n;
-    HIPCHK(ensure_pinned(sg.host, sg.host_ints, ints));
+    // (grown by doubling: trajectories get longer with every turn, and a new block
+    // takes allocations and, for the old one, a device synchronisation)
+    if (ints > sg.host_ints)
+      HIPCHK(ensure_pinned(sg.host, sg.host_ints, std::max({ints, 2 * sg.host_ints, kStageInts})));
     HIPCHK(sg.dev.ensure(sg.host_ints * 4));
     size_t at = 0;
     auto put = [&](const void* src, size_t count) {
@@ -1488,7 +1492,8 @@ war_status war_debug_workspace(war_model* m, const char* name, void** ptr, int64
       {"P", w.P, w.p_elems * 4}, {"pm", w.pm, pr * 4}, {"pl", w.pl, pr * 4}, {"po", w.po, pr * md.hd * 4},
       {"rows", w.rows, 4 * R * 4}, {"reqs", w.reqs, 4 * (int64_t)w.n_req_cap * 4},
       {"items", w.items, w.items_cap * 16}, {"order", w.order, w.items_cap * 4}, {"n_items", w.n_items, 16},
-      {"tree", w.tree, 2 * R * 4}};
+      {"tree", w.tree, 2 * R * 4},
+      {"stage", m->stage[0].dev.p, (int64_t)m->stage[0].dev.bytes}};
   for (const Entry& e : table)
     if (n == e.name) {
       *ptr = const_cast<void*>(e.p);

@@ -136,3 +136,27 @@ def test_large_lm_head_rows_match_small_steps(rows, d):
     ref = torch.cat([step(lo, min(rows, lo + 27))[0] for lo in range(0, rows, 27)])
     assert (got[0] - ref).abs().max() <= LOGIT_TOL
     assert torch.equal(got[1].long(), (got[0] == got[0].amax(-1, keepdim=True)).int().argmax(-1))
+
+
+def test_append_metadata_grows_in_few_steps():
+    """A trajectory that gets a little longer with every append: the metadata block
+    is allocated a few times in all, not at every turn."""
+    import ctypes as C
+
+    from paper_2607_17299_amd import war
+    cfg = synth.reduced(synth.TINY, 1)
+    w = {n: t.to(DEV) for n, t in synth.model_weights(cfg, seed=0, norm_std=0.1).items()}
+    model, pool = war.Model(cfg, w, max_rows=4096), war.Pool(cfg, 4000, 1, 4000)
+    ctx, nxt, sizes = _t([0]), _t([0]), set()
+    for turn in range(1, 64):
+        n = 7 * turn
+        war.prefill_append(model, pool, _t([0]), ctx, [n], _t(np.arange(n) % cfg.vocab), nxt)
+        p, size = C.c_void_p(), C.c_int64()
+        assert war.lib().war_debug_workspace(model.handle, b"stage", C.byref(p), C.byref(size)) == 0
+        sizes.add(size.value)
+    assert int(ctx[0]) == 7 * 63 * 32 and len(sizes) <= 2
+    n = 4 * 4096 - 100                     # more rows than any append before it
+    war.prefill_append(model, pool, _t([0]), ctx, [n], _t(np.arange(n) % cfg.vocab), nxt)
+    torch.cuda.synchronize()
+    assert war.lib().war_debug_workspace(model.handle, b"stage", C.byref(p), C.byref(size)) == 0
+    assert size.value >= 2 * max(sizes) or size.value == max(sizes)
