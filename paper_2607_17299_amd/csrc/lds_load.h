@@ -2,8 +2,11 @@
 // Written as asm because the compiler waits for every such load in flight before
 // any LDS read (it cannot tell stages apart): whoever issues one waits for it with
 // s_waitcnt vmcnt before a barrier.  There is no output register; m0 is set for
-// each load, one wait state before it is used, and has no other user in the
-// kernels that include this.
+// each load, one wait state before it is used.  The compiler keeps m0 reserved (it
+// cannot be named as clobbered) and does not look into asm for hazards, so nothing
+// else in the kernels that include this may use m0, and no vector instruction may
+// write a load's scalar operands just before it: test_lds_load_asm.py reads their
+// assembly for both.
 #pragma once
 
 #include <type_traits>
