@@ -430,37 +430,35 @@ void launch_argmax(const GemmArgs& g, hipStream_t st) {
   else k_gemm<MT, 0, EPI_ARGMAX><<<grid, 256, 0, st>>>(g);
 }
 
+// The partial sums of splits of one of STEPS k-steps; false for another count.
+template <int MT, int... STEPS>
+bool launch_unrolled(const GemmArgs& g, dim3 grid, hipStream_t st) {
+  return ((g.kper == STEPS * KS && (k_gemm<MT, STEPS, EPI_PARTIAL><<<grid, 256, 0, st>>>(g), true)) || ...);
+}
+
 template <int MT>
 void launch_mt(const GemmArgs& g, int epi, int splits, hipStream_t st) {
+  constexpr bool kQuarters = MT == 3 || MT == 4;  // 64-step gate/up and 8- to 64-step splits: launch_x2c_64
   dim3 grid(g.N / 128, splits, 1);
   const int steps = g.kper / KS;
-  const bool exact = (int64_t)g.kper * splits == g.K;
   if (epi == EPI_ARGMAX) {
     launch_argmax<MT>(g, st);
   } else if (epi == EPI_SWIGLU) {
-    if (steps == 64) k_gemm<MT, 64, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
-    else if (steps == 16) k_gemm<MT, 16, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
+    if constexpr (!kQuarters)
+      if (steps == 64) {
+        k_gemm<MT, 64, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
+        return;
+      }
+    if (steps == 16) k_gemm<MT, 16, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
     else k_gemm<MT, 0, EPI_SWIGLU><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 1) {
-    k_gemm<MT, 1, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 2) {
-    k_gemm<MT, 2, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 24) {
-    k_gemm<MT, 24, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 4) {
-    k_gemm<MT, 4, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 8) {
-    k_gemm<MT, 8, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 12) {
-    k_gemm<MT, 12, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 16) {
-    k_gemm<MT, 16, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 32) {
-    k_gemm<MT, 32, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
-  } else if (exact && steps == 48) {
-    k_gemm<MT, 48, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
   } else {
-    k_gemm<MT, 0, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
+    bool done = false;
+    if ((int64_t)g.kper * splits == g.K) {
+      if constexpr (kQuarters) done = launch_unrolled<MT, 1, 2, 4, 12>(g, grid, st);
+      else if constexpr (MT == 5) done = launch_unrolled<MT, 1, 2, 4, 12, 32, 48>(g, grid, st);  // 8, 16, 24: launch_x2c_80
+      else done = launch_unrolled<MT, 1, 2, 4, 8, 12, 16, 24, 32, 48>(g, grid, st);
+    }
+    if (!done) k_gemm<MT, 0, EPI_PARTIAL><<<grid, 256, 0, st>>>(g);
   }
 }
 

@@ -298,9 +298,12 @@ void go(const GemmArgs& g, int epi, int splits, hipStream_t st) {
   if constexpr (BN == 128 && !WNT)
     if (g.M <= BM) return go<BM, BN, WM, WN, LPS, ST, true>(g, epi, splits, st);
   const dim3 grid(cdiv_i(g.N, BN) * cdiv_i(g.M, BM), splits);
-  if (epi == EPI_SWIGLU)
-    k_gemm_tile<BM, BN, WM, WN, LPS, ST, EPI_SWIGLU, WNT><<<grid, kThreads, 0, st>>>(g);
-  else if (epi == EPI_PARTIAL)
+  if constexpr (BM != 2 * BN)  // (gate/up matrices are whole 256-column tiles: 128 x 256 is never worse)
+    if (epi == EPI_SWIGLU) {
+      k_gemm_tile<BM, BN, WM, WN, LPS, ST, EPI_SWIGLU, WNT><<<grid, kThreads, 0, st>>>(g);
+      return;
+    }
+  if (epi == EPI_PARTIAL)
     k_gemm_tile<BM, BN, WM, WN, LPS, ST, EPI_PARTIAL, WNT><<<grid, kThreads, 0, st>>>(g);
   else
     k_gemm_tile<BM, BN, WM, WN, LPS, ST, EPI_ARGMAX, WNT><<<grid, kThreads, 0, st>>>(g);
@@ -321,7 +324,8 @@ constexpr TileShape kTiles[] = {{256, 256, 1.29f}, {192, 256, 1.06f}, {128, 256,
 // memory (0.19 us a MB) and 0.3 us a split for their consumer.  Over 19 row
 // counts from 96 to 2048 of the 4096-wide decoder's four projections the choices
 // take 1% more in all than the best of every shape and 1, 2, 3, 4, 6 or 8 splits
-// (5.1 ms together; the skinny kernels took 6.8).
+// (5.1 ms together; the skinny kernels took 6.8).  256 x 128 only differs from
+// 128 x 256 in what an odd number of 128-column groups wastes.
 TilePlan plan_gemm_tile(int M, int N, int K, int epi, int64_t cap_elems) {
   const int steps = K / KS;
   TilePlan best{-1, 1, K};

@@ -49,3 +49,22 @@ def test_splits_cover_k_within_the_cap(d):
                 if s == 0:
                     continue
                 assert kper % 64 == 0 and (s - 1) * kper < K <= s * kper and s * M * N <= cap
+
+
+@pytest.mark.parametrize("M,N,K,epi,shape", [
+    (193, 12288, 4096, PARTIAL, 0), (512, 24576, 4096, ARGMAX, 0), (512, 24576, 4096, SWIGLU, 0),
+    (129, 12288, 4096, PARTIAL, 1), (257, 24576, 4096, ARGMAX, 1), (257, 24576, 4096, SWIGLU, 1),
+    (81, 12288, 4096, PARTIAL, 2), (193, 24576, 4096, ARGMAX, 2), (193, 24576, 4096, SWIGLU, 2),
+    (193, 6528, 4096, PARTIAL, 3), (1280, 6528, 4096, ARGMAX, 3),
+    (129, 6144, 4096, PARTIAL, 4), (129, 24576, 4096, ARGMAX, 4), (129, 24576, 4096, SWIGLU, 4),
+    (81, 4096, 4096, PARTIAL, 5), (81, 4096, 4096, ARGMAX, 5), (81, 1024, 4096, SWIGLU, 5)])
+def test_tile_shapes(M, N, K, epi, shape):
+    """Every kernel there is has sizes that take it."""
+    assert _plan(M, N, K, epi)[0] == shape
+
+
+def test_gate_up_never_takes_the_256_by_128_tile():
+    """(It has no such kernel.)"""
+    for N in range(256, 65537, 256):
+        for M in (81, 128, 129, 192, 256, 257, 300, 384, 512, 600, 768, 1000, 1152, 1280, 1536, 2048, 4096, 65536):
+            assert _plan(M, N, 64, SWIGLU)[0] not in (-1, 3)
