@@ -48,6 +48,18 @@ war_status war_debug_sample(const float* logits, int32_t V, int32_t B, int32_t k
 war_status war_debug_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epi, int64_t cap_elems, int32_t* shape,
                                int32_t* splits, int32_t* kper);
 
+/* One product of A [M][K] with W [N][K] (device bf16, row-major; packed here)
+ * through a chosen kernel.  epi as above; SwiGLU takes the gate and up halves
+ * ([N/2][K] each) as W and W2.  shape: a tile shape, or -1 for the few-row
+ * kernels (at most 80 rows, the argmax 96).  splits x kper cover K (one split
+ * but for partial sums).  a_rows (nullable, argmax): row m reads A row
+ * a_rows[m].  out: fp32 partial sums [splits][M][N], fp32 logits [M][N] with
+ * amax_v / amax_i [M][N/128] the best of each 128 columns, or bf16 [M][N/2].
+ * Synchronises the stream. */
+war_status war_debug_gemm(const void* A, const void* W, const void* W2, int32_t M, int32_t N, int32_t K, int32_t epi,
+                          int32_t shape, int32_t splits, int32_t kper, const int32_t* a_rows, void* out,
+                          float* amax_v, int32_t* amax_i, void* stream);
+
 /* How many times the pool's verify steps read the exact free page count from
  * the device (each such read waits for the stream) because the host's lower
  * bound did not cover the step's worst-case reservation (HOST out). */

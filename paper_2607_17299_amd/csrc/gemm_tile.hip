@@ -314,7 +314,7 @@ struct TileShape {
   int bm, bn;
   float step_us;
 };
-constexpr TileShape kTiles[] = {{256, 256, 1.29f}, {192, 256, 1.06f}, {128, 256, 0.77f},
+constexpr TileShape kTiles[kTileShapes] = {{256, 256, 1.29f}, {192, 256, 1.06f}, {128, 256, 0.77f},
                                 {256, 128, 0.77f}, {192, 128, 0.64f}, {128, 128, 0.48f}};
 
 }  // namespace
@@ -330,7 +330,7 @@ TilePlan plan_gemm_tile(int M, int N, int K, int epi, int64_t cap_elems) {
   const int steps = K / KS;
   TilePlan best{-1, 1, K};
   float best_us = 1e30f;
-  for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
+  for (int c = 0; c < kTileShapes; ++c) {
     const TileShape& t = kTiles[c];
     for (int s = 1; s <= (epi == EPI_PARTIAL ? std::min(8, steps) : 1); ++s) {
       const int per = cdiv_i(steps, s);

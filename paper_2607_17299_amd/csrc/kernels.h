@@ -129,6 +129,7 @@ inline bool gemm_tiled(int M, int N, int epi) { return M > (epi == EPI_ARGMAX &&
 struct TilePlan {
   int shape, splits, kper;
 };
+constexpr int kTileShapes = 6;
 TilePlan plan_gemm_tile(int M, int N, int K, int epi, int64_t cap_elems);
 void launch_gemm_tile(const GemmArgs& g, int epi, int shape, int splits, hipStream_t st);
 // W [N][K] row-major -> dst in MFMA fragment order; N % 16 == 0, K % 64 == 0

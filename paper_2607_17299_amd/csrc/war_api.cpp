@@ -1470,6 +1470,51 @@ war_status war_debug_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epi, int
   return WAR_OK;
 }
 
+war_status war_debug_gemm(const void* A, const void* W, const void* W2, int32_t M, int32_t N, int32_t K, int32_t epi,
+                          int32_t shape, int32_t splits, int32_t kper, const int32_t* a_rows, void* out,
+                          float* amax_v, int32_t* amax_i, void* stream) {
+  CHECK(epi == EPI_PARTIAL || epi == EPI_ARGMAX || epi == EPI_SWIGLU, "bad epilogue");
+  CHECK(A && W && out && (epi != EPI_SWIGLU || W2) && (epi != EPI_ARGMAX || (amax_v && amax_i)), "null array");
+  CHECK(aligned16(A) && aligned16(W) && aligned16(W2), "unaligned operand");
+  CHECK(M >= 1 && N >= 128 && N % 128 == 0 && K >= 64 && K % 64 == 0, "bad sizes");
+  CHECK((int64_t)N * K * 2 <= 0x3fffffff && (int64_t)M * K * 2 <= 0x3fffffff, "operands of 1 GiB or more");
+  CHECK(epi != EPI_SWIGLU || N % 256 == 0, "gate and up halves are multiples of 128 columns");
+  CHECK(!a_rows || epi == EPI_ARGMAX, "gathered rows are the LM head's");
+  if (shape < 0) CHECK(M <= (epi == EPI_ARGMAX ? 96 : 80), "too many rows for the few-row kernels");
+  else CHECK(shape < kTileShapes && !(epi == EPI_SWIGLU && shape == 3), "no such tile");
+  CHECK(splits >= 1 && splits <= 64 && kper >= 64 && kper % 64 == 0 && (int64_t)(splits - 1) * kper < K &&
+            (int64_t)splits * kper >= K, "splits do not cover K");
+  CHECK(epi == EPI_PARTIAL || splits == 1, "one split but for partial sums");
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  DevBuf packed;
+  HIPCHK(packed.ensure((size_t)N * K * 2));
+  launch_pack_weights(static_cast<const bf16_t*>(W), epi == EPI_SWIGLU ? static_cast<const bf16_t*>(W2) : nullptr, N, K,
+                      packed.as<bf16_t>(), st);
+  GemmArgs g{};
+  g.A = static_cast<const bf16_t*>(A);
+  g.lda = K;
+  g.a_rows = a_rows;
+  g.Wp = packed.as<bf16_t>();
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.kper = kper;
+  g.out = static_cast<bf16_t*>(out);
+  g.ld_out = N / 2;
+  g.P = static_cast<float*>(out);
+  g.logits = static_cast<float*>(out);
+  g.ld_logits = N;
+  g.amax_v = amax_v;
+  g.amax_i = amax_i;
+  if (shape >= 0) launch_gemm_tile(g, epi, shape, splits, st);
+  else launch_gemm(g, epi, splits, st);
+  hipError_t e = hipGetLastError();
+  const hipError_t es = hipStreamSynchronize(st);
+  packed.release();
+  HIPCHK(e == hipSuccess ? es : e);
+  return WAR_OK;
+}
+
 war_status war_debug_pool_waits(war_kv_pool* p, int64_t* waits) {
   CHECK(p && waits, "null argument");
   *waits = p->exact_waits;

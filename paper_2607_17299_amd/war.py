@@ -29,7 +29,7 @@ EXPORTS = ["war_weight_count", "war_model_create", "war_model_destroy", "war_kv_
            "war_verify_step_noalloc",
            "war_kv_commit", "war_pool_state",
            "war_last_error", "war_debug_mfma16", "war_debug_workspace", "war_debug_sample",
-           "war_debug_gemm_plan", "war_debug_pool_waits", "war_profile", "war_profile_read"]
+           "war_debug_gemm", "war_debug_gemm_plan", "war_debug_pool_waits", "war_profile", "war_profile_read"]
 
 
 class WarError(RuntimeError):
@@ -72,6 +72,7 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
         "war_debug_sample": (i32, [vp, i32, i32, i32, vp, vp, vp, C.c_float, i32, vp, vp, vp]),
         "war_debug_mfma16": (i32, [vp, vp, vp, vp]),
         "war_debug_workspace": (i32, [vp, C.c_char_p, C.POINTER(vp), C.POINTER(C.c_int64)]),
+        "war_debug_gemm": (i32, [vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp]),
         "war_debug_gemm_plan": (i32, [i32, i32, i32, i32, C.c_int64, pi32, pi32, pi32]),
         "war_debug_pool_waits": (i32, [vp, C.POINTER(C.c_int64)]),
         "war_profile": (i32, [vp, i32]),
@@ -323,6 +324,22 @@ def debug_gemm_plan(M: int, N: int, K: int, epi: int, cap_elems: int = 64 << 20)
     out = [C.c_int32() for _ in range(3)]
     _check(lib().war_debug_gemm_plan(M, N, K, epi, cap_elems, *[C.byref(x) for x in out]))
     return tuple(x.value for x in out)
+
+
+def debug_gemm(A: torch.Tensor, W: torch.Tensor, epi: int, shape: int, splits: int = 1, kper: int = 0,
+               W2: Optional[torch.Tensor] = None, a_rows: Optional[torch.Tensor] = None, stream=None):
+    """One product through a chosen kernel (war_debug.h): partial sums [splits, M, N],
+    (logits [M, N], block maxima, their columns) or the SwiGLU output [M, N / 2]."""
+    M = A.shape[0] if a_rows is None else a_rows.numel()
+    N, K = W.shape[0] * (2 if W2 is not None else 1), A.shape[1]
+    dev = A.device
+    best = (torch.zeros((M, N // 128), device=dev), torch.zeros((M, N // 128), dtype=torch.int32, device=dev))
+    out = (torch.full((splits, M, N), float("nan"), device=dev) if epi == 0 else
+           torch.full((M, N), float("nan"), device=dev) if epi == 1 else
+           torch.full((M, N // 2), float("nan"), dtype=torch.bfloat16, device=dev))
+    _check(lib().war_debug_gemm(_ptr(A), _ptr(W), _ptr(W2), M, N, K, epi, shape, splits, kper or K, _ptr(a_rows),
+                                _ptr(out), _ptr(best[0]), _ptr(best[1]), _stream(stream)))
+    return (out, *best) if epi == 1 else out
 
 
 def debug_workspace(model: Model, name: str, dtype: torch.dtype, shape) -> torch.Tensor:

@@ -1,8 +1,9 @@
 """Passes of more than 80 rows (the tiled GEMM, gemm_tile.hip) against the same
 rows in passes of at most 80 (the skinny kernels, which the oracle tests cover
 at full widths): one layer of the 36-layer shapes under a head of 33 128-id
-blocks, so that a 256-column tile ends half empty.  Row counts sit at the edges
-of the row tiles (128, 192, 256) and of the first row count that takes them.
+blocks.  Row counts sit at the edges of the row tiles (128, 192, 256) and of the
+first row count that takes them.  (These sizes take four of the six tiles;
+test_gpu_gemm.py runs every kernel by itself, half-empty tiles among them.)
 Both sides sum in fp32 over the same bf16 rounding points: they differ where a
 value falls on the other side of a rounding, within the bound the oracle
 comparison uses for up to two layers (5e-2 on the logits, 3e-2 on K and V)."""
