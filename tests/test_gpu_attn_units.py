@@ -164,3 +164,30 @@ def test_shortened_chunks_leave_at_most_64_partials(lens, keys):
     pool.alloc(list(range(B)), lens)
     items, _, _, got = _plan(war, model, pool, lens, 0)
     assert got == keys and len(items) == sum(-(-(n + 1) // keys) for n in lens)
+
+
+@pytest.mark.parametrize("shape,k", [("tiny", 1), ("tiny", 2), ("tiny", 4), ("tiny", 8), ("large", 1), ("large", 2),
+                                     ("large", 4), ("large", 8)])
+def test_shared_pages_of_siblings_with_drafts(models, shape, k):
+    """Five siblings with full drafts: a run holds as many consecutive members as have
+    their rows fit the step's row block together (with more drafts, one), its first
+    member owns the shared chunks, each run's once."""
+    from parity import shared_units
+    war, by_name = models
+    cfg, model = by_name[shape]
+    pages, B, G = 130, 5, cfg.group
+    lens = [pages * 16 + n for n in (40, 3, 200, 77, 12)]
+    pool = war.Pool(cfg, B * (pages + 20), B, pages + 60)
+    pool.kv.zero_()
+    pool.alloc([0], [lens[0]])
+    for s in range(1, B):
+        pool.fork(0, s, pages * 16)
+    pool.alloc(list(range(1, B)), lens[1:])
+    items, order, n_units, chunk = _plan(war, model, pool, lens, k)
+    rows = G * (k + 1)
+    runs = shared_units([rows] * B, 16 if rows <= 16 else 32 if rows <= 32 else 48)
+    own = [x for r in runs for x in [r] + [-1] * (r - 1)]
+    shared, n = pages * 16 // 1024, [-(-(x + k + 1) // 1024) for x in lens]
+    assert chunk == 1024 and n_units == sum(n) - (B - len(runs)) * shared
+    assert items.tolist() == [[b, 0, c, own[b] if c < shared else 0] for b in range(B) for c in range(n[b])]
+    assert sorted(order.tolist()) == [i for i, it in enumerate(items.tolist()) if it[3] >= 0]

@@ -2,7 +2,7 @@
 rows in passes of at most 80 (the skinny kernels, which the oracle tests cover
 at full widths): one layer of the 36-layer shapes under a head of 33 128-id
 blocks.  Row counts sit at the edges of the row tiles (128, 192, 256) and of the
-first row count that takes them.  (These sizes take four of the six tiles;
+first row count that takes them.  (These sizes take five of the six tiles;
 test_gpu_gemm.py runs every kernel by itself, half-empty tiles among them.)
 Both sides sum in fp32 over the same bf16 rounding points: they differ where a
 value falls on the other side of a rounding, within the bound the oracle
