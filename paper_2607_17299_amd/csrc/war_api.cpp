@@ -396,9 +396,12 @@ Split pick_split(int M, int N, int K, int64_t cap_elems) {
   return unrolled(most) || cost(most) <= cost(few) ? most : few;
 }
 
-// The count the workspace of a step is sized by (the partial sums of all its
-// projections share one buffer): the fewest exact splits with >= 192 workgroups
-// over m-blocks of up to 96 rows and at most 48 steps of 64 per split.
+// The count that sizes the partial sums of a pass (all its projections share one
+// buffer) and so bounds every choice above and plan_gemm_tile's: the fewest exact
+// splits of at most 48 k-steps with >= 192 workgroups, a workgroup per 96 rows (at
+// 97-192 rows one for both).  It stays as it is whatever the kernels do: which steps
+// war_verify_step_noalloc takes hangs on it.  As a choice it is the alternative of
+// pick_split, for few rows.
 Split bound_split(int M, int N, int K, int64_t cap_elems) {
   const int tiles = std::max(1, cdiv_i(M, 16));
   const int mt = tiles <= 6 ? tiles : cdiv_i(tiles, cdiv_i(tiles, 6));  // balanced m-blocks of at most 6 tiles
@@ -408,7 +411,7 @@ Split bound_split(int M, int N, int K, int64_t cap_elems) {
     if (K % (s * 64)) continue;
     if ((int64_t)base * s >= 192 && K / (s * 64) <= 48 && (int64_t)s * M * N <= cap_elems) return {s, K / s};
   }
-  // fall back: one split per 1024 of K (runtime-loop kernel)
+  // none: one split per 1024 of K (runtime-loop kernel)
   int s = std::max(1, K / 1024);
   while (s > 1 && (int64_t)s * M * N > cap_elems) --s;
   const int kper = cdiv_i(cdiv_i(K, s), 64) * 64;
