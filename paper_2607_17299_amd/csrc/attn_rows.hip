@@ -16,13 +16,13 @@
 //     lane order (each lane names its own 16 bytes), so that fragment reads are
 //     contiguous.  Four stages each, keys requested four steps and values two
 //     before the step that holds them: a load has two steps to arrive.
-// 2048 rows of 32 heads over 25600 keys (head_dim 128): 1403 -> 1151-1162 us, 1.11
-// PFLOP/s with the hi and lo products counted (a large bf16 matrix product 1.3-1.57),
-// the matrix pipes busy 64% of the cycles (the kernel it replaces, which staged
-// blocks through registers and took scores, softmax and product one after the
-// other: 41%) at the 1.7 GHz the card then runs.  Fewer VALU instructions (the low
-// parts by v_dot2c_f32_bf16: 1185 us) or addresses (per-lane ones: 1151) change
-// nothing.
+// 2048 rows of 32 heads over 25600 keys (head_dim 128): 1403 -> 1151-1162 us (the
+// kernel it replaces staged blocks through registers and took scores, softmax and
+// product one after the other).  Over an append of 16 x 2048 tokens to 8192-26624 keys
+// the matrix pipes are busy 60% of all cycles (41% before), 1.12 PFLOP/s executed, the
+// masked keys of the last blocks and both halves of P counted (a large bf16 matrix
+// product 1.3-1.57).  Fewer VALU instructions (the low parts by v_dot2c_f32_bf16: 1185
+// us) or addresses (per-lane ones: 1151) change nothing.
 #include "attn.h"
 #include "lds_load.h"
 

@@ -1,6 +1,6 @@
 // Tiled bf16 GEMM on gfx950 MFMA for many rows: the projections of prefill
-// chunks and wide verify batches, and their LM head (more than 80 rows; fewer
-// run in gemm.hip's skinny kernels).
+// chunks and wide verify batches, and their LM head (more than 80 rows, a large LM
+// head more than 96; fewer run in gemm.hip's skinny kernels).
 //
 // C[m][n] = sum_k A[m][k] * W[n][k] over the packed weights of gemm.hip (1 KB
 // MFMA fragments, step-major).  At these sizes the matrix cores bound it, so a
@@ -19,8 +19,9 @@
 // Measured (4096-wide decoder, weights rotated), against the skinny kernels that
 // ran these rows before: qkv / o / gate+up / down at 256 rows 28 / 19 / 86 / 48 us
 // -> 19 / 14 / 57 / 33; at 1152 rows 74 / 44 / 249 / 141 -> 53 / 39 / 199 / 98; at
-// 2048 rows 130 / 85 / 477 / 263 -> 93 / 58 / 308 / 153 (1340 TFLOP/s), the matrix
-// pipes busy 70% of the cycles a workgroup is resident.
+// 2048 rows 130 / 85 / 477 / 263 -> 93 / 58 / 308 / 153 (1340 TFLOP/s); over a
+// long append's passes of 2048 rows the matrix pipes are busy 62% (gate/up), 59%
+// (down), 48% (o) and 42% (qkv, 192 tiles on 256 CUs) of all cycles.
 #include "lds_load.h"
 
 namespace {

@@ -41,7 +41,7 @@ struct VerifySetupArgs {
   int32_t* unit_ctr;  // attention work counters, cleared here
   int chunk;         // keys per attention item; doubled when that still leaves
   int items_double;  // at least this many items (enough to fill the attention grid),
-  int items_fill;    // halved while that leaves at most this many
+  int items_fill;    // halved while that leaves at most this many and no request too many partials
   int G;        // query heads per kv-head
   int rb;       // attention row block of the step (rows per unit)
   int cascade;  // 1: plan shared-prefix attention units for forked siblings
